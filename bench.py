@@ -42,7 +42,7 @@ def alg_bytes(storage: str, ncomp: int = 2, c_ns: int = 1) -> int:
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("lbm_kernels.hip", "lbm_kernels.h"):
+    for f in ("lbm_device.h", "lbm_kernels.hip", "lbm_kernels.h"):
         with open(os.path.join(ROOT, "paper_2206_11524_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
