@@ -12,7 +12,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libhmcsc.so")
-SOURCES = ["lbm_kernels.hip", "lbm_runtime.cpp", "lbm_batch.cpp", "lbm_noalloc.hip"]
+SOURCES = ["lbm_kernels.hip", "lbm_box.hip", "lbm_runtime.cpp", "lbm_batch.cpp", "lbm_noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -40,6 +40,7 @@ struct Launch {
     int tile_y;   // rows per tile (split layout: 4 with 128-wide rows, 4 or 8 with 64, 4, 8
                   // or 16 with 32; pair layout: 4 or pair_tile_y() with 64)
     int zchunk;   // planes per block
+    int bx, by, bz;  // cells per block of the box kernel (small domains); bx = 0: the sweep
 };
 
 // True if two components in this format use the pair layout: both values of
@@ -62,6 +63,16 @@ int storage_bytes(int storage);
 // t is the time step of the state in A (keys the stochastic rounding).
 hipError_t launch_step(const Problem& p, const Launch& l, int64_t t, const void* A, void* B,
                        const float* ns, hipStream_t s);
+
+// The same step by the box kernel (one box of l.bx x l.by x l.bz cells per
+// block), for domains whose boxes fit (box_fits).
+bool box_fits(const Problem& p, int bx, int by, int bz);
+
+// The box for a domain small enough to gain from it; false: use the sweep.
+bool choose_box(const Problem& p, int cus, int* bx, int* by, int* bz);
+
+hipError_t launch_step_box(const Problem& p, const Launch& l, int64_t t, const void* A, void* B,
+                           const float* ns, hipStream_t s);
 
 // t = 0 state: rest equilibrium of rho_init (device FP64 [ncomp][N]).
 hipError_t launch_init(const Problem& p, const double* rho_init, void* A, hipStream_t s);

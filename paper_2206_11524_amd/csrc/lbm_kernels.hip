@@ -1429,6 +1429,7 @@ static hipError_t step_st(const Problem& p, const Launch& l, int64_t t, const vo
 hipError_t launch_step(const Problem& p, const Launch& l, int64_t t, const void* A, void* B, const float* ns,
                        hipStream_t st)
 {
+    if (l.bx > 0) return launch_step_box(p, l, t, A, B, ns, st);
     switch (p.storage) {
     case kF64: return step_st<F64>(p, l, t, A, B, ns, st);
     case kF32: return step_st<F32>(p, l, t, A, B, ns, st);

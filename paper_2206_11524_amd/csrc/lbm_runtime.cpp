@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -94,6 +95,18 @@ int env_int(const char* name, int dflt)
 hm::Launch choose_launch(const hm::Problem& p, int cus)
 {
     hm::Launch l{};
+    // small domains: the box kernel, unless a tile or chunk of the sweep is
+    // asked for (LBM_BOX = "bx,by,bz" sets the box, "0" keeps to the sweep)
+    const char* box = std::getenv("LBM_BOX");
+    if (box && *box) {
+        int d[3] = {0, 0, 0};
+        if (std::sscanf(box, "%d,%d,%d", d, d + 1, d + 2) == 3 && hm::box_fits(p, d[0], d[1], d[2])) {
+            l.bx = d[0]; l.by = d[1]; l.bz = d[2];
+        }
+    } else if (!env_int("LBM_TILE_X", 0) && !env_int("LBM_TILE_Y", 0) && !env_int("LBM_ZCHUNK", 0) &&
+               !hm::choose_box(p, cus, &l.bx, &l.by, &l.bz)) {
+        l.bx = 0;
+    }
     // FP64 with two components needs the smaller tile to stay within the
     // register file (no spills); the pair kernel runs one thread per cell
     // plus three ring waves on 64-wide tiles of pair_tile_y() rows
