@@ -37,9 +37,16 @@ class BatchRunner {
   public:
     ~BatchRunner() { release(); }
 
-    int init(int storage, int ncomp, int c_ns, int tile_x, int tile_y, int max_domains, int k_graph,
+    // tile_x, tile_y: tile of every domain, 0: the pair layout takes each
+    // domain's own (Launch::batch_x, batch_y), the split layout 64 x 8.  nt: the
+    // store policy whose graphs are captured now (the other's when a tick needs
+    // them).
+    int init(int storage, int ncomp, int c_ns, int tile_x, int tile_y, int max_domains, int k_graph, bool nt,
              hipStream_t st)
     {
+        own_tiles_ = !tile_x && !tile_y && hm::pair_layout(storage, ncomp);
+        if (!tile_x) tile_x = 64;
+        if (!tile_y) tile_y = 8;
         storage_ = storage;
         ncomp_ = ncomp;
         c_ns_ = c_ns;
@@ -70,8 +77,15 @@ class BatchRunner {
         }
         HIP_TRY(hipEventCreate(&t0_));
         HIP_TRY(hipEventCreate(&t1_));
-        // graphs of kmax launches, one per table copy
         graphs_ok_ = true;
+        capture(nt);
+        return LBM_OK;
+    }
+
+    // Graphs of kmax launches with one store policy, one per table copy.
+    void capture(bool nt)
+    {
+        hipGraphExec_t(&exec)[2] = exec_[nt ? 1 : 0];
         for (int j = 0; j < 2 && graphs_ok_; ++j) {
             hipGraph_t g = nullptr;
             if (hipStreamBeginCapture(stream_, hipStreamCaptureModeRelaxed) != hipSuccess) {
@@ -80,7 +94,7 @@ class BatchRunner {
             }
             bool ok = true;
             for (int k = 0; k < kmax_; ++k)
-                ok = ok && hm::launch_step_batch(storage_, ncomp_, c_ns_, tx_, ty_, dev_[j], k, grid_, stream_) ==
+                ok = ok && hm::launch_step_batch(storage_, ncomp_, c_ns_, tx_, ty_, dev_[j], k, grid_, nt, stream_) ==
                                hipSuccess;
             if (hipStreamEndCapture(stream_, &g) != hipSuccess || !ok || !g) {
                 graphs_ok_ = false;
@@ -88,11 +102,19 @@ class BatchRunner {
                 (void)hipGetLastError();
                 break;
             }
-            if (hipGraphInstantiate(&exec_[j], g, nullptr, nullptr, 0) != hipSuccess) graphs_ok_ = false;
+            if (hipGraphInstantiate(&exec[j], g, nullptr, nullptr, 0) != hipSuccess) graphs_ok_ = false;
             (void)hipGraphDestroy(g);
         }
         (void)hipGetLastError();
-        return LBM_OK;
+    }
+
+    // Whole 128-byte lines in every row of the domain's tiles: non-temporal
+    // stores; otherwise the rows' shared lines are merged in the caches.
+    static bool whole_lines(const hm::BatchDomain& d)
+    {
+        if (!hm::pair_layout(d.prob.storage, d.prob.ncomp)) return true;  // one policy
+        const int64_t word = 2 * hm::storage_bytes(d.prob.storage);
+        return d.tile_x * word % 128 == 0 && d.prob.nx * word % 128 == 0;
     }
 
     // k launches over the n domains (k <= kmax uses the graph when k == kmax).
@@ -108,8 +130,14 @@ class BatchRunner {
         // re-reads cost little there)
         balanced_.assign(d, d + n);
         int64_t cols = 0, tiles16 = 0;
-        for (const hm::BatchDomain& b : balanced_) {
-            const int64_t c = static_cast<int64_t>((b.prob.nx + tx_ - 1) / tx_) * ((b.prob.ny + ty_ - 1) / ty_);
+        bool nt = true;
+        for (hm::BatchDomain& b : balanced_) {
+            if (!own_tiles_) {
+                b.tile_x = tx_;
+                b.tile_y = ty_;
+            }
+            nt = nt && whole_lines(b);
+            const int64_t c = columns(b);
             cols += c;
             tiles16 += c * ((b.prob.nz + 15) / 16);
         }
@@ -132,15 +160,16 @@ class BatchRunner {
         std::stable_sort(balanced_.begin(), balanced_.end(), [](const hm::BatchDomain& a, const hm::BatchDomain& b) {
             return a.zchunk > b.zchunk;
         });
-        hm::batch_encode(storage_, balanced_.data(), n, tx_, ty_, host_[j]);
+        hm::batch_encode(storage_, balanced_.data(), n, host_[j]);
         HIP_TRY(hipMemcpyAsync(dev_[j], host_[j], bytes_, hipMemcpyHostToDevice, stream_));
         HIP_TRY(hipEventRecord(copied_[j], stream_));
         HIP_TRY(hipEventRecord(t0_, stream_));
+        if (k == kmax_ && graphs_ok_ && !exec_[nt ? 1 : 0][0]) capture(nt);
         if (k == kmax_ && graphs_ok_) {
-            HIP_TRY(hipGraphLaunch(exec_[j], stream_));
+            HIP_TRY(hipGraphLaunch(exec_[nt ? 1 : 0][j], stream_));
         } else {
             for (int kk = 0; kk < k; ++kk)
-                HIP_TRY(hm::launch_step_batch(storage_, ncomp_, c_ns_, tx_, ty_, dev_[j], kk, grid_, stream_));
+                HIP_TRY(hm::launch_step_batch(storage_, ncomp_, c_ns_, tx_, ty_, dev_[j], kk, grid_, nt, stream_));
         }
         HIP_TRY(hipEventRecord(t1_, stream_));
         last_k_ = k;
@@ -163,11 +192,13 @@ class BatchRunner {
     {
         if (stream_) (void)hipStreamSynchronize(stream_);
         for (int j = 0; j < 2; ++j) {
-            if (exec_[j]) (void)hipGraphExecDestroy(exec_[j]);
+            for (int q = 0; q < 2; ++q) {
+                if (exec_[q][j]) (void)hipGraphExecDestroy(exec_[q][j]);
+                exec_[q][j] = nullptr;
+            }
             if (dev_[j]) (void)hipFree(dev_[j]);
             if (host_[j]) (void)hipHostFree(host_[j]);
             if (copied_[j]) (void)hipEventDestroy(copied_[j]);
-            exec_[j] = nullptr;
             dev_[j] = nullptr;
             host_[j] = nullptr;
             copied_[j] = nullptr;
@@ -178,6 +209,12 @@ class BatchRunner {
     }
 
   private:
+    static int64_t columns(const hm::BatchDomain& b)
+    {
+        return static_cast<int64_t>((b.prob.nx + b.tile_x - 1) / b.tile_x) *
+               ((b.prob.ny + b.tile_y - 1) / b.tile_y);
+    }
+
     // Chunks per tile column shared by the domains of balanced_ (each capped
     // by chunk_of).  Blocks take tiles w, w + G, w + 2G, ... of the table
     // (G = grid_, tiles ordered longest first, each domain's tiles chunk by
@@ -224,7 +261,7 @@ class BatchRunner {
             int64_t w = 0;
             for (const auto& o : order) {
                 const hm::BatchDomain& b = balanced_[static_cast<size_t>(o.second)];
-                const int64_t tcols = static_cast<int64_t>((b.prob.nx + tx_ - 1) / tx_) * ((b.prob.ny + ty_ - 1) / ty_);
+                const int64_t tcols = columns(b);
                 for (int64_t z0 = 0; z0 < b.prob.nz; z0 += o.first) {
                     const int64_t len = std::min<int64_t>(o.first, b.prob.nz - z0) + kTileCost;
                     for (int64_t t = 0; t < tcols; ++t, ++w) load[static_cast<size_t>(w % grid_)] += len;
@@ -252,7 +289,8 @@ class BatchRunner {
     void* dev_[2] = {nullptr, nullptr};
     char* host_[2] = {nullptr, nullptr};
     hipEvent_t copied_[2] = {nullptr, nullptr};
-    hipGraphExec_t exec_[2] = {nullptr, nullptr};
+    hipGraphExec_t exec_[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};  // [store policy][table copy]
+    bool own_tiles_ = false;
     bool graphs_ok_ = false;
     int slot_ = 0;
     hipEvent_t t0_ = nullptr, t1_ = nullptr;
@@ -264,6 +302,8 @@ hm::BatchDomain domain_of(const lbm_ctx* c, int steps)
     hm::BatchDomain d{};
     d.prob = c->prob;
     d.zchunk = c->prob.nz;  // set per launch by BatchRunner::run
+    d.tile_x = c->launch.batch_x;
+    d.tile_y = c->launch.batch_y;
     d.buf[0] = c->buf[0];
     d.buf[1] = c->buf[1];
     d.ns = c->ns;
@@ -317,11 +357,10 @@ int lbm_group_create(lbm_ctx* const* ctxs, int32_t n, lbm_group** out)
     if (!g) return LBM_ENOMEM;
     g->ctx.assign(ctxs, ctxs + n);
     const lbm_params& p = ctxs[0]->prm;
-    int tx = 64, ty = 8;
-    hm::batch_default_tile(p.storage, p.ncomp, &tx, &ty);
-    tx = hm_rt::env_int("LBM_BATCH_TILE_X", tx);
-    ty = hm_rt::env_int("LBM_BATCH_TILE_Y", ty);
-    const int rc = g->runner.init(p.storage, p.ncomp, p.c_ns, tx, ty, n, hm_rt::env_int("LBM_GRAPH_STEPS", 16),
+    const int tx = hm_rt::env_int("LBM_BATCH_TILE_X", 0), ty = hm_rt::env_int("LBM_BATCH_TILE_Y", 0);
+    bool nt = true;
+    for (const lbm_ctx* c : g->ctx) nt = nt && BatchRunner::whole_lines(domain_of(c, 0));
+    const int rc = g->runner.init(p.storage, p.ncomp, p.c_ns, tx, ty, n, hm_rt::env_int("LBM_GRAPH_STEPS", 16), nt,
                                   ctxs[0]->stream);
     if (rc) {
         delete g;
@@ -915,11 +954,8 @@ int lbm_server_create(const lbm_server_cfg* cfg, void* reserved, lbm_server** ou
     if (cfg->policy < LBM_SERVE_FAIR || cfg->policy > LBM_SERVE_SHORTEST_FIRST || cfg->pad != 0 ||
         cfg->run_cells < 0)
         return LBM_EINVAL;
-    int tx = 64, ty = 8;
-    hm::batch_default_tile(cfg->storage, cfg->ncomp, &tx, &ty);
-    if (cfg->tile_x) tx = cfg->tile_x;
-    if (cfg->tile_y) ty = cfg->tile_y;
-    if (!hm::batch_tile_supported(cfg->storage, cfg->ncomp, tx, ty)) return LBM_EINVAL;
+    const int tx = cfg->tile_x, ty = cfg->tile_y;
+    if (!hm::batch_tile_supported(cfg->storage, cfg->ncomp, tx ? tx : 64, ty ? ty : 8)) return LBM_EINVAL;
     lbm_server* s = new (std::nothrow) lbm_server();
     if (!s) return LBM_ENOMEM;
     s->cfg = *cfg;
@@ -965,7 +1001,7 @@ int lbm_server_create(const lbm_server_cfg* cfg, void* reserved, lbm_server** ou
     s->budget = cfg->hbm_budget_bytes ? cfg->hbm_budget_bytes : static_cast<uint64_t>(0.9 * free_b);
     s->pool.init(s->budget, uint64_t(8) << 30);
     const int rc = s->runner.init(cfg->storage, cfg->ncomp, cfg->c_ns, tx, ty, cfg->max_slots, cfg->steps_per_tick,
-                                  s->stream);
+                                  false, s->stream);
     if (rc) return fail(rc);
     s->worker = std::thread([s] { s->run(); });
     *out = s;

@@ -272,11 +272,11 @@ __device__ __forceinline__ W word_load(rsrc_t r, uint32_t vo, uint32_t so)
     else return __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0);
 }
 
-template <typename W>
+template <typename W, int AUX>
 __device__ __forceinline__ void word_store(W v, rsrc_t r, uint32_t vo, uint32_t so)
 {
-    if constexpr (sizeof(W) == 8) __builtin_amdgcn_raw_buffer_store_b64(v, r, vo, so, kNT);
-    else __builtin_amdgcn_raw_buffer_store_b32(v, r, vo, so, kNT);
+    if constexpr (sizeof(W) == 8) __builtin_amdgcn_raw_buffer_store_b64(v, r, vo, so, AUX);
+    else __builtin_amdgcn_raw_buffer_store_b32(v, r, vo, so, AUX);
 }
 
 // Kernel parameters in the arithmetic type.
@@ -287,6 +287,7 @@ struct Args {
     int64_t N;   // cells
     int pair;    // populations in the pair layout
     int zchunk, ntx, nty, nzc;
+    int tw, th;  // tile of the pair sweep
     T inv_tau[2], tau[2];
     T G_s, Gads_s[2];
     T F[3];

@@ -36,11 +36,12 @@ struct Problem {
 };
 
 struct Launch {
-    int tile_x;   // cells per tile row (32, 64 or 128)
-    int tile_y;   // rows per tile (split layout: 4 with 128-wide rows, 4 or 8 with 64, 4, 8
-                  // or 16 with 32; pair layout: 4 or pair_tile_y() with 64)
+    int tile_x;   // cells per tile row and rows per tile: 128 x 4, 64 x 4 or 8, 32 x 4, 8 or 16
+    int tile_y;   // in the split layout; any up to 64 x 16 of at most 512 cells in the pair layout
     int zchunk;   // planes per block
+    bool nt_stores;  // pair layout: non-temporal stores
     int bx, by, bz;  // cells per block of the box kernel (small domains); bx = 0: the sweep
+    int batch_x, batch_y;  // tile in a batched launch (pair layout)
 };
 
 // True if two components in this format use the pair layout: both values of
@@ -48,9 +49,6 @@ struct Launch {
 // the GS-WBS keeps the split layout), plane blocks [z][i][y][x][s]; all other
 // runs use the split layout [s][z][i][y][x].
 bool pair_layout(int storage, int ncomp, int forcing = kForcingShanChen);
-
-// Rows of the default tile of the pair kernel (64 cells wide).
-int pair_tile_y();
 
 // True if the tile shape is compiled in for this format, component count and
 // forcing scheme.
@@ -135,6 +133,7 @@ hipError_t launch_flux(const Problem& p, int axis, const double* rho, const doub
 struct BatchDomain {
     Problem prob;
     int zchunk;
+    int tile_x, tile_y;
     const void* buf[2];  // population buffers (ping-pong)
     const float* ns;
     int parity;          // buffer holding the state before the first launch of the tick
@@ -147,20 +146,22 @@ size_t batch_table_bytes(int storage, int max_domains);
 
 // Encode the table for n domains into host memory (batch_table_bytes bytes);
 // returns the total number of tiles.  Upload it to the device before launching.
-int batch_encode(int storage, const BatchDomain* d, int n, int tile_x, int tile_y, void* host);
+int batch_encode(int storage, const BatchDomain* d, int n, void* host);
 
-// Tile shapes compiled for the batched kernel, and the default one.
+// Tile shapes that may be asked of the batched kernel (64 x 8, and 32 x 8 in
+// the split layout).
 bool batch_tile_supported(int storage, int ncomp, int tile_x, int tile_y);
-void batch_default_tile(int storage, int ncomp, int* tile_x, int* tile_y);
 
 // Blocks of the batched kernel that fit one CU at once (registers, LDS); at
 // least 1.
 int batch_blocks_per_cu(int storage, int ncomp, int c_ns, int tile_x, int tile_y);
 
 // Launch k of a tick: every domain with k < steps takes one step.  The grid
-// strides over all tiles of the table, so any fixed grid size works.
+// strides over all tiles of the table, so any fixed grid size works.  In the
+// split layout every domain has the tile tile_x x tile_y; nt: non-temporal
+// stores (pair layout).
 hipError_t launch_step_batch(int storage, int ncomp, int c_ns, int tile_x, int tile_y, const void* table, int k,
-                             int grid, hipStream_t st);
+                             int grid, bool nt, hipStream_t st);
 
 // Convergence monitor (server): one domain of a monitor table.
 struct MonitorDomain {

@@ -484,61 +484,67 @@ __device__ __forceinline__ void step_tile(const Args<typename ST::T>& a, const t
 // from LDS, so no register holds them while two planes of loads are in
 // flight.  FP32: one plane (its words take twice the room), the plane being
 // collided in registers, one plane of loads in flight.
-template <typename ST, int CNS, int TX, int TY>
+//
+// A tile is any w x h cells of at most 512, rows of up to 64: the host fits it
+// to the domain (choose_launch), and the lanes take its cells row by row
+// without gaps, so a width that is no multiple of 64 leaves few lanes idle.  A
+// plane costs a block 3.5 us of its CU's issue slots and waits in 16 bits, with
+// or without idle lanes, against 3.7 us of HBM time for 512 cells with every CU
+// at work: on ragged domains idle lanes were the bound (131^3 in FP16, 66 % of
+// the lanes: 136 us a step with 64 x 8 tiles, 108 with 44 x 11).  The LDS row
+// stride stays 66, so that every stencil offset is an instruction's immediate
+// (a run-time stride cost FP32 eight registers and spilled); the words come
+// first in LDS because their 78 KB reach past the 64 KB of such offsets.
+constexpr int kPairCells = 512;    // cells of a tile (one thread each), at most
+constexpr int kPairW = 64;         // cells of a tile row, at most
+constexpr int kPairH = 16;         // rows of a tile, at most
+constexpr int kPairStaged = 660;   // cells of a tile with its ring, at most (64 x 8)
+constexpr int kPairRing = 192;     // ring / n_s threads per block (three waves)
+static_assert(2 * (kPairW + 2) + 2 * kPairH <= kPairRing, "one ring cell per ring thread");
+
+template <typename ST, int CNS>
 struct PairShared {
     using W = typename PairWordOf<ST>::W;
-    static constexpr int LW = TX + 2;
-    static constexpr int LP = LW * (TY + 2);
-    static constexpr int NT = TX * TY;
+    static constexpr int LW = kPairW + 2;
+    static constexpr int LP = LW * (kPairH + 2);
+    static constexpr int NT = kPairCells;
     static constexpr int NB = sizeof(W) == 4 ? 2 : 1;  // planes of words held in LDS
+    W hs[NB][kQ][NT];
     float rho[4][2][LP];
     float ns[4][CNS][LP];
-    W hs[NB][kQ][NT];
 };
-
-constexpr int kPairRing = 192;  // ring / n_s threads per block (three waves)
-#ifndef LBM_PAIR_TY
-#define LBM_PAIR_TY 8
-#endif
-// Rows of the default pair tile (64 x kPairTY cells).  With eight rows the
-// block has eight cell waves, an even share for each of a CU's four SIMDs (nine
-// leave one SIMD a third collision per plane), and a 256 x 256 plane splits
-// into 128 tile columns, so two z-chunks per column give one block for each of
-// 256 CUs (nine rows: 116 columns, 232 blocks).
-constexpr int kPairTY = LBM_PAIR_TY;
 
 // Planes a cell wave keeps in flight ahead of the one it stages (1 or 2).
 #ifndef LBM_PAIR_AHEAD
 #define LBM_PAIR_AHEAD 2
 #endif
 
-template <typename ST, int CNS, int TX, int TY, int FS, bool ONE, int RND>
+template <typename ST, int CNS, int FS, bool ONE, int RND, int AUX>
 __device__ __forceinline__ void step_tile_pair(const Args<float>& a,
                                                const typename PairWordOf<ST>::W* __restrict__ A,
                                                typename PairWordOf<ST>::W* __restrict__ B,
                                                const float* __restrict__ ns, int L, uint32_t t,
-                                               PairShared<ST, CNS, TX, TY>& sh)
+                                               PairShared<ST, CNS>& sh)
 {
     using T = float;
     using W = typename PairWordOf<ST>::W;
-    constexpr int LW = TX + 2;
-    constexpr int LP = LW * (TY + 2);
-    constexpr int NT = TX * TY;
+    constexpr int LW = PairShared<ST, CNS>::LW, LP = PairShared<ST, CNS>::LP;
+    constexpr int NT = kPairCells;
     constexpr int NR = kPairRing;
-    constexpr int NSR = (LP + NR - 1) / NR;  // n_s cells staged per ring thread and plane
+    constexpr int NSR = (kPairStaged + NR - 1) / NR;  // n_s cells staged per ring thread and plane
     static_assert(NT % 64 == 0, "the roles must fill whole waves");
-    static_assert(2 * (TX + 2) + 2 * TY <= NR, "one ring cell per ring thread");
     auto& s_rho = sh.rho;
     auto& s_ns = sh.ns;
 
     const int tx = L % a.ntx;
     const int ty = (L / a.ntx) % a.nty;
     const int tz = L / (a.ntx * a.nty);
-    const int x0 = tx * TX, y0 = ty * TY;
+    const int x0 = tx * a.tw, y0 = ty * a.th;
     const int zs = tz * a.zchunk;
     const int ze = min(zs + a.zchunk, a.nz);
-    const int TXe = min(TX, a.nx - x0);
-    const int TYe = min(TY, a.ny - y0);
+    const int TXe = min(a.tw, a.nx - x0);
+    const int TYe = min(a.th, a.ny - y0);
+    const TileGeom<LW, LP> geo;
     const int plane = a.plane;
     const int tl = static_cast<int>(threadIdx.x);
 
@@ -647,12 +653,13 @@ __device__ __forceinline__ void step_tile_pair(const Args<float>& a,
     }
 
     // ---- cell waves ----
-    const int lx = tl % TX;
-    const int ly = tl / TX;
-    // a lane beyond a ragged tile edge duplicates the last active lane of its
-    // row / column (same cell, same LDS slots, identical values written twice)
-    const int x = x0 + min(lx, TXe - 1);
-    const int y = y0 + min(ly, TYe - 1);
+    // lanes take the tile's cells row by row, without gaps; a lane beyond the
+    // last cell duplicates it (same cell, same LDS slots, identical values
+    // written twice)
+    const int cq = min(tl, TXe * TYe - 1);
+    const int ly = cq / TXe;
+    const int x = x0 + (cq - ly * TXe);
+    const int y = y0 + ly;
     const int me = (y - y0 + 1) * LW + (x - x0 + 1);
     const PlaneOffs qme = plane_offs<sizeof(W)>(x, y, a.nx, a.ny);
     const uint32_t own = static_cast<uint32_t>(y * a.nx + x) * static_cast<uint32_t>(sizeof(W));
@@ -661,7 +668,6 @@ __device__ __forceinline__ void step_tile_pair(const Args<float>& a,
 
     // Collision of plane z from the words wd of the own cell and the LDS slots
     // of planes z-1, z, z+1.
-    const TileGeom<LW, LP> geo;
     auto collide = [&](int z, int sm, int s0, int sp, const T (&jm)[6], auto&& wd) {
         const rsrc_t rz = blk(B, z);
         const uint32_t cell =
@@ -669,7 +675,7 @@ __device__ __forceinline__ void step_tile_pair(const Args<float>& a,
         pair_collide<ST, CNS, FS, RND>(
             geo, a, cxy | reservoir_z_bits(a, z), t_key, cell, me, &s_rho[sm][0][0], &s_rho[s0][0][0], &s_rho[sp][0][0],
             &s_ns[sm][0][0], &s_ns[s0][0][0], &s_ns[sp][0][0], jm, wd,
-            [&](int i, W v) { word_store<W>(v, rz, own, static_cast<uint32_t>(i) * dir_bytes); });
+            [&](int i, W v) { word_store<W, AUX>(v, rz, own, static_cast<uint32_t>(i) * dir_bytes); });
     };
 
     if constexpr (ONE) {
@@ -785,9 +791,9 @@ __device__ __forceinline__ void step_tile_pair(const Args<float>& a,
 }
 
 template <typename ST, int NC, int TX, int TY, int FS = kForcingShanChen>
-constexpr int kThreads = kPair<ST, NC, FS> ? TX * TY + kPairRing : NC * TX * TY;
+constexpr int kThreads = kPair<ST, NC, FS> ? kPairCells + kPairRing : NC * TX * TY;
 
-template <typename ST, int NC, int CNS, int TX, int TY, int FS, bool ONE, int RND>
+template <typename ST, int NC, int CNS, int TX, int TY, int FS, bool ONE, int RND, int AUX>
 __global__ __launch_bounds__((kThreads<ST, NC, TX, TY, FS>)) void k_step(Args<typename ST::T> a,
                                                                     const typename ST::E* __restrict__ A,
                                                                     typename ST::E* __restrict__ B,
@@ -796,8 +802,8 @@ __global__ __launch_bounds__((kThreads<ST, NC, TX, TY, FS>)) void k_step(Args<ty
     const int L = xcd_tile(blockIdx.x, gridDim.x);
     if constexpr (kPair<ST, NC, FS>) {
         using W = typename PairWordOf<ST>::W;
-        __shared__ PairShared<ST, CNS, TX, TY> sh;
-        step_tile_pair<ST, CNS, TX, TY, FS, ONE, RND>(a, reinterpret_cast<const W*>(A), reinterpret_cast<W*>(B), ns, L,
+        __shared__ PairShared<ST, CNS> sh;
+        step_tile_pair<ST, CNS, FS, ONE, RND, AUX>(a, reinterpret_cast<const W*>(A), reinterpret_cast<W*>(B), ns, L,
                                                       a.t, sh);
     } else {
         __shared__ TileShared<ST, NC, CNS, TX, TY> sh;
@@ -831,7 +837,7 @@ struct BatchHeader {
 
 constexpr size_t kBatchEntryOffset = 64;
 
-template <typename ST, int NC, int CNS, int TX, int TY>
+template <typename ST, int NC, int CNS, int TX, int TY, int AUX>
 __global__ __launch_bounds__((kThreads<ST, NC, TX, TY>)) void k_step_batch(const char* __restrict__ table, int k)
 {
     using T = typename ST::T;
@@ -845,7 +851,7 @@ __global__ __launch_bounds__((kThreads<ST, NC, TX, TY>)) void k_step_batch(const
     // (neighbouring tiles re-read each other's edge cells through its L2)
     const int nb = gridDim.x;
     const int b0 = (nb & 7) == 0 ? (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
-    using Shared = std::conditional_t<kPair<ST, NC>, PairShared<ST, CNS, TX, TY>, TileShared<ST, NC, CNS, TX, TY>>;
+    using Shared = std::conditional_t<kPair<ST, NC>, PairShared<ST, CNS>, TileShared<ST, NC, CNS, TX, TY>>;
     __shared__ Shared sh;
     for (int w = b0; w < total; w += nb) {
         int lo = 0, hi = nd - 1;  // last domain with tile_begin <= w
@@ -865,13 +871,12 @@ __global__ __launch_bounds__((kThreads<ST, NC, TX, TY>)) void k_step_batch(const
             const W* src = static_cast<const W*>(e.buf[cur]);
             W* dst = static_cast<W*>(const_cast<void*>(e.buf[1 - cur]));
             const uint32_t tk = e.a.t + static_cast<uint32_t>(k);
-            constexpr int SR = sizeof(E) == 2 ? kRoundStochastic : kRoundNearest;
-            if (e.a.sr)
-                step_tile_pair<ST, CNS, TX, TY, kForcingShanChen, false, SR>(e.a, src, dst, e.ns, w - e.tile_begin,
-                                                                             tk, sh);
+            if (sizeof(E) == 2 && e.a.sr)
+                step_tile_pair<ST, CNS, kForcingShanChen, false, sizeof(E) == 2 ? kRoundStochastic : kRoundNearest,
+                               AUX>(e.a, src, dst, e.ns, w - e.tile_begin, tk, sh);
             else
-                step_tile_pair<ST, CNS, TX, TY, kForcingShanChen, false, kRoundNearest>(e.a, src, dst, e.ns,
-                                                                                      w - e.tile_begin, tk, sh);
+                step_tile_pair<ST, CNS, kForcingShanChen, false, kRoundNearest, AUX>(e.a, src, dst, e.ns,
+                                                                                     w - e.tile_begin, tk, sh);
         } else
             step_tile<ST, NC, CNS, TX, TY, kForcingShanChen>(e.a, static_cast<const E*>(e.buf[cur]),
                                                              static_cast<E*>(const_cast<void*>(e.buf[1 - cur])), e.ns,
@@ -1329,11 +1334,11 @@ bool pair_layout(int storage, int ncomp, int forcing)
     return ((storage == kF32 && forcing != kForcingGuo) || storage == kF16 || storage == kBF16) && ncomp == 2;
 }
 
-int pair_tile_y() { return kPairTY; }
 
 bool tile_supported(int storage, int ncomp, int tx, int ty, int forcing)
 {
-    if (pair_layout(storage, ncomp, forcing)) return tx == 64 && (ty == kPairTY || ty == 4);
+    if (pair_layout(storage, ncomp, forcing))
+        return tx >= 1 && ty >= 1 && tx <= kPairW && ty <= kPairH && tx * ty <= kPairCells;
     return (tx == 128 && ty == 4) || (tx == 64 && (ty == 4 || ty == 8)) || (tx == 32 && (ty == 4 || ty == 8 || ty == 16));
 }
 
@@ -1356,43 +1361,44 @@ static hipError_t step_t(const Problem& p, const Launch& l, int64_t t, const voi
     using E = typename ST::E;
     Args<T> a = make_args<T>(p);
     a.zchunk = l.zchunk;
-    a.ntx = (p.nx + TX - 1) / TX;
-    a.nty = (p.ny + TY - 1) / TY;
+    a.tw = l.tile_x;
+    a.th = l.tile_y;
+    a.ntx = (p.nx + l.tile_x - 1) / l.tile_x;
+    a.nty = (p.ny + l.tile_y - 1) / l.tile_y;
     a.nzc = (p.nz + l.zchunk - 1) / l.zchunk;
     a.t = static_cast<uint32_t>(t);
     const int nblocks = a.ntx * a.nty * a.nzc;
     // the pair kernel is compiled per rounding mode; the split kernels
     // branch on it (their two store sequences are alike)
+    // and per store policy
+    auto go = [&](auto rnd, auto aux) {
+        hipLaunchKernelGGL((k_step<ST, NC, CNS, TX, TY, FS, ONE, decltype(rnd)::value, decltype(aux)::value>),
+                           dim3(nblocks), dim3(kThreads<ST, NC, TX, TY, FS>), 0, st, a, static_cast<const E*>(A),
+                           static_cast<E*>(B), ns);
+    };
+    using Nt = std::integral_constant<int, kNT>;
     if constexpr (kPair<ST, NC, FS>) {
-        constexpr int SR = sizeof(E) == 2 ? kRoundStochastic : kRoundNearest;  // FP32 rounds to nearest
-        if (p.stochastic)
-            hipLaunchKernelGGL((k_step<ST, NC, CNS, TX, TY, FS, ONE, SR>), dim3(nblocks),
-                               dim3(kThreads<ST, NC, TX, TY, FS>), 0, st, a, static_cast<const E*>(A),
-                               static_cast<E*>(B), ns);
-        else
-            hipLaunchKernelGGL((k_step<ST, NC, CNS, TX, TY, FS, ONE, kRoundNearest>), dim3(nblocks),
-                               dim3(kThreads<ST, NC, TX, TY, FS>), 0, st, a, static_cast<const E*>(A),
-                               static_cast<E*>(B), ns);
+        // FP32 rounds to nearest; one plane (and the GS-WBS) keep one policy
+        using Sr = std::integral_constant<int, sizeof(E) == 2 ? kRoundStochastic : kRoundNearest>;
+        using Near = std::integral_constant<int, kRoundNearest>;
+        constexpr bool BOTH = !ONE && FS == kForcingShanChen;
+        using Cached = std::integral_constant<int, BOTH ? 0 : kNT>;
+        const bool cached = BOTH && !l.nt_stores;
+        if (p.stochastic) cached ? go(Sr{}, Cached{}) : go(Sr{}, Nt{});
+        else cached ? go(Near{}, Cached{}) : go(Near{}, Nt{});
     } else {
-        hipLaunchKernelGGL((k_step<ST, NC, CNS, TX, TY, FS, ONE, kRoundEither>), dim3(nblocks),
-                           dim3(kThreads<ST, NC, TX, TY, FS>), 0, st, a, static_cast<const E*>(A), static_cast<E*>(B),
-                           ns);
+        go(std::integral_constant<int, kRoundEither>{}, Nt{});
     }
     return hipGetLastError();
 }
 
-// The default tiles of a layout, with the one-plane and GS-WBS instances.
-template <typename ST, int NC, int CNS, int TX, int TY>
-static hipError_t step_default(const Problem& p, const Launch& l, int64_t t, const void* A, void* B, const float* ns,
-                               hipStream_t st)
+// One forcing scheme, with its one-plane instance.
+template <typename ST, int NC, int CNS, int TX, int TY, int FS>
+static hipError_t step_fs(const Problem& p, const Launch& l, int64_t t, const void* A, void* B, const float* ns,
+                          hipStream_t st)
 {
-    constexpr int SC = kForcingShanChen, GUO = kForcingGuo;
-    const bool one = p.nz == 1;
-    if (p.forcing == kForcingGuo)
-        return one ? step_t<ST, NC, CNS, TX, TY, GUO, true>(p, l, t, A, B, ns, st)
-                   : step_t<ST, NC, CNS, TX, TY, GUO, false>(p, l, t, A, B, ns, st);
-    return one ? step_t<ST, NC, CNS, TX, TY, SC, true>(p, l, t, A, B, ns, st)
-               : step_t<ST, NC, CNS, TX, TY, SC, false>(p, l, t, A, B, ns, st);
+    return p.nz == 1 ? step_t<ST, NC, CNS, TX, TY, FS, true>(p, l, t, A, B, ns, st)
+                     : step_t<ST, NC, CNS, TX, TY, FS, false>(p, l, t, A, B, ns, st);
 }
 
 // Tile shapes (TX x TY cells per block) compiled in.
@@ -1400,15 +1406,25 @@ template <typename ST, int NC, int CNS>
 static hipError_t step_ty(const Problem& p, const Launch& l, int64_t t, const void* A, void* B, const float* ns,
                           hipStream_t st)
 {
-    constexpr int SC = kForcingShanChen;
+    constexpr int SC = kForcingShanChen, GUO = kForcingGuo;
+    if (!tile_supported(p.storage, NC, l.tile_x, l.tile_y, p.forcing)) return hipErrorInvalidValue;
+    const bool t8 = l.tile_x == 64 && l.tile_y == 8, t4 = l.tile_x == 64 && l.tile_y == 4;
+    if (p.forcing == GUO) {
+        if constexpr (kPair<ST, NC, GUO>) {
+            return step_fs<ST, NC, CNS, 64, 8, GUO>(p, l, t, A, B, ns, st);
+        } else {
+            if (t8) return step_fs<ST, NC, CNS, 64, 8, GUO>(p, l, t, A, B, ns, st);
+            if (t4) return step_fs<ST, NC, CNS, 64, 4, GUO>(p, l, t, A, B, ns, st);
+            return hipErrorInvalidValue;  // default tiles only
+        }
+    }
     if constexpr (kPair<ST, NC>) {
-        if (l.tile_x == 64 && l.tile_y == kPairTY) return step_default<ST, NC, CNS, 64, kPairTY>(p, l, t, A, B, ns, st);
-        if (l.tile_x == 64 && l.tile_y == 4) return step_default<ST, NC, CNS, 64, 4>(p, l, t, A, B, ns, st);
-        return hipErrorInvalidValue;
+        // one instance takes every tile (the 64, 8 only name it)
+        return step_fs<ST, NC, CNS, 64, 8, SC>(p, l, t, A, B, ns, st);
     } else {
-        if (l.tile_x == 64 && l.tile_y == 8) return step_default<ST, NC, CNS, 64, 8>(p, l, t, A, B, ns, st);
-        if (l.tile_x == 64 && l.tile_y == 4) return step_default<ST, NC, CNS, 64, 4>(p, l, t, A, B, ns, st);
-        if (p.forcing == kForcingGuo || p.nz == 1) return hipErrorInvalidValue;  // default tiles only
+        if (t8) return step_fs<ST, NC, CNS, 64, 8, SC>(p, l, t, A, B, ns, st);
+        if (t4) return step_fs<ST, NC, CNS, 64, 4, SC>(p, l, t, A, B, ns, st);
+        if (p.nz == 1) return hipErrorInvalidValue;  // default tiles only
         if (l.tile_x == 128 && l.tile_y == 4) return step_t<ST, NC, CNS, 128, 4, SC, false>(p, l, t, A, B, ns, st);
         if (l.tile_x == 32 && l.tile_y == 4) return step_t<ST, NC, CNS, 32, 4, SC, false>(p, l, t, A, B, ns, st);
         if (l.tile_x == 32 && l.tile_y == 8) return step_t<ST, NC, CNS, 32, 8, SC, false>(p, l, t, A, B, ns, st);
@@ -1725,7 +1741,7 @@ size_t batch_table_bytes(int storage, int max_domains)
 }
 
 template <typename T>
-static int batch_encode_t(const BatchDomain* d, int n, int tile_x, int tile_y, void* host)
+static int batch_encode_t(const BatchDomain* d, int n, void* host)
 {
     BatchHeader* h = static_cast<BatchHeader*>(host);
     BatchEntry<T>* e = reinterpret_cast<BatchEntry<T>*>(static_cast<char*>(host) + kBatchEntryOffset);
@@ -1733,8 +1749,10 @@ static int batch_encode_t(const BatchDomain* d, int n, int tile_x, int tile_y, v
     for (int i = 0; i < n; ++i) {
         Args<T> a = make_args<T>(d[i].prob);
         a.zchunk = d[i].zchunk;
-        a.ntx = (d[i].prob.nx + tile_x - 1) / tile_x;
-        a.nty = (d[i].prob.ny + tile_y - 1) / tile_y;
+        a.tw = d[i].tile_x;
+        a.th = d[i].tile_y;
+        a.ntx = (d[i].prob.nx + a.tw - 1) / a.tw;
+        a.nty = (d[i].prob.ny + a.th - 1) / a.th;
         a.nzc = (d[i].prob.nz + a.zchunk - 1) / a.zchunk;
         a.t = static_cast<uint32_t>(d[i].t);
         e[i].a = a;
@@ -1753,16 +1771,23 @@ static int batch_encode_t(const BatchDomain* d, int n, int tile_x, int tile_y, v
     return tiles;
 }
 
-int batch_encode(int storage, const BatchDomain* d, int n, int tile_x, int tile_y, void* host)
+int batch_encode(int storage, const BatchDomain* d, int n, void* host)
 {
-    return storage == kF64 ? batch_encode_t<double>(d, n, tile_x, tile_y, host)
-                           : batch_encode_t<float>(d, n, tile_x, tile_y, host);
+    return storage == kF64 ? batch_encode_t<double>(d, n, host) : batch_encode_t<float>(d, n, host);
+}
+
+// Kernel of a store policy (the split layout has one).
+template <typename ST, int NC, int CNS, int TX, int TY>
+static auto batch_kernel(bool nt)
+{
+    constexpr int CACHED = kPair<ST, NC> ? 0 : kNT;
+    return nt ? k_step_batch<ST, NC, CNS, TX, TY, kNT> : k_step_batch<ST, NC, CNS, TX, TY, CACHED>;
 }
 
 template <typename ST, int NC, int CNS, int TX, int TY>
-static hipError_t batch_t(const void* table, int k, int grid, hipStream_t st)
+static hipError_t batch_t(const void* table, int k, int grid, bool nt, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_step_batch<ST, NC, CNS, TX, TY>), dim3(grid), dim3(kThreads<ST, NC, TX, TY>), 0, st,
+    hipLaunchKernelGGL((batch_kernel<ST, NC, CNS, TX, TY>(nt)), dim3(grid), dim3(kThreads<ST, NC, TX, TY>), 0, st,
                        static_cast<const char*>(table), k);
     return hipGetLastError();
 }
@@ -1771,8 +1796,8 @@ template <typename ST, int NC, int CNS, int TX, int TY>
 static int batch_occ_t()
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step_batch<ST, NC, CNS, TX, TY>, kThreads<ST, NC, TX, TY>,
-                                                     0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<ST, NC, CNS, TX, TY>(true),
+                                                     kThreads<ST, NC, TX, TY>, 0) != hipSuccess)
         return 1;
     return n > 0 ? n : 1;
 }
@@ -1783,12 +1808,13 @@ template <typename ST, int NC, int CNS, typename F>
 static hipError_t batch_tile(int tx, int ty, F&& f)
 {
     if constexpr (kPair<ST, NC>) {
-        if (tx == 64 && ty == kPairTY) return f(batch_t<ST, NC, CNS, 64, kPairTY>, batch_occ_t<ST, NC, CNS, 64, kPairTY>);
+        // one instance takes every tile (the 64, 8 only name it)
+        return f(batch_t<ST, NC, CNS, 64, 8>, batch_occ_t<ST, NC, CNS, 64, 8>);
     } else {
         if (tx == 64 && ty == 8) return f(batch_t<ST, NC, CNS, 64, 8>, batch_occ_t<ST, NC, CNS, 64, 8>);
         if (tx == 32 && ty == 8) return f(batch_t<ST, NC, CNS, 32, 8>, batch_occ_t<ST, NC, CNS, 32, 8>);
+        return hipErrorInvalidValue;
     }
-    return hipErrorInvalidValue;
 }
 
 template <typename F>
@@ -1804,14 +1830,8 @@ static hipError_t batch_dispatch(int storage, int ncomp, int c_ns, int tx, int t
 
 bool batch_tile_supported(int storage, int ncomp, int tx, int ty)
 {
-    if (pair_layout(storage, ncomp)) return tx == 64 && ty == kPairTY;
+    if (pair_layout(storage, ncomp)) return tx == 64 && ty == 8;
     return (tx == 64 && ty == 8) || (tx == 32 && ty == 8);
-}
-
-void batch_default_tile(int storage, int ncomp, int* tx, int* ty)
-{
-    *tx = 64;
-    *ty = pair_layout(storage, ncomp) ? kPairTY : 8;
 }
 
 int batch_blocks_per_cu(int storage, int ncomp, int c_ns, int tile_x, int tile_y)
@@ -1825,10 +1845,10 @@ int batch_blocks_per_cu(int storage, int ncomp, int c_ns, int tile_x, int tile_y
 }
 
 hipError_t launch_step_batch(int storage, int ncomp, int c_ns, int tile_x, int tile_y, const void* table, int k,
-                             int grid, hipStream_t st)
+                             int grid, bool nt, hipStream_t st)
 {
     return batch_dispatch(storage, ncomp, c_ns, tile_x, tile_y,
-                          [&](auto launch, auto) { return launch(table, k, grid, st); });
+                          [&](auto launch, auto) { return launch(table, k, grid, nt, st); });
 }
 
 }  // namespace hm

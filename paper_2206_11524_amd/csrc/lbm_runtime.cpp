@@ -108,52 +108,101 @@ hm::Launch choose_launch(const hm::Problem& p, int cus)
         l.bx = 0;
     }
     // FP64 with two components needs the smaller tile to stay within the
-    // register file (no spills); the pair kernel runs one thread per cell
-    // plus three ring waves on 64-wide tiles of pair_tile_y() rows
+    // register file (no spills)
     const bool wide = p.storage == hm::kF64 && p.ncomp == 2;
     const bool pair = hm::pair_layout(p.storage, p.ncomp, p.forcing);
-    const int pty = hm::pair_tile_y();
-    const int dflt_y = pair ? (p.ny >= pty ? pty : 4) : ((p.ny >= 8 && !wide) ? 8 : 4);
-    l.tile_x = env_int("LBM_TILE_X", 64);
-    l.tile_y = env_int("LBM_TILE_Y", dflt_y);
-    // the GS-WBS and one-plane domains use the default tile widths only
-    if (!hm::tile_supported(p.storage, p.ncomp, l.tile_x, l.tile_y, p.forcing) ||
-        ((p.forcing == hm::kForcingGuo || p.nz == 1) &&
-         !(l.tile_x == 64 && (pair ? (l.tile_y == pty || l.tile_y == 4) : (l.tile_y == 8 || l.tile_y == 4))))) {
+    const int dflt_y = (p.ny >= 8 && !wide) ? 8 : 4;
+    const int env_x = env_int("LBM_TILE_X", 0), env_y = env_int("LBM_TILE_Y", 0), env_z = env_int("LBM_ZCHUNK", 0);
+    l.tile_x = env_x ? env_x : 64;
+    l.tile_y = env_y ? env_y : dflt_y;
+    const bool given = hm::tile_supported(p.storage, p.ncomp, l.tile_x, l.tile_y, p.forcing) &&
+                       (pair || !(p.forcing == hm::kForcingGuo || p.nz == 1) ||
+                        (l.tile_x == 64 && (l.tile_y == 8 || l.tile_y == 4)));
+    if (!given) {  // the split GS-WBS and one-plane domains use the default widths only
         l.tile_x = 64;
         l.tile_y = dflt_y;
     }
-    const int ntx = (p.nx + l.tile_x - 1) / l.tile_x;
-    const int nty = (p.ny + l.tile_y - 1) / l.tile_y;
-    const int64_t cols = static_cast<int64_t>(ntx) * nty;
-    int zc = env_int("LBM_ZCHUNK", 0);
-    if (zc <= 0) {
-        // One block fits a CU (registers and LDS), so blocks run in rounds
-        // of one per CU, and a block takes about (chunk + 8) plane times: the
-        // halo planes, the pipeline fill and drain and the block's start cost
-        // as much as about eight planes (fitted to timings of 192^3 to 384^3
-        // domains).  Take the chunking with the least rounds x (chunk + 8),
-        // the fewest chunks among equals.
-        // Chunks shorter than 16 planes spend too much on their halo, unless
-        // the domain would then give fewer than two such tiles per CU: a
-        // small domain would leave most CUs idle, and its halo re-reads are
-        // L2 hits.
-        const int64_t ncu = std::max(cus, 1);
+    const int64_t ncu = std::max(cus, 1);
+    const int64_t word = 2 * hm::storage_bytes(p.storage);
+    // One block fits a CU (registers and LDS), so blocks run in rounds of one
+    // per CU, and a block takes about (chunk + 8) plane times: the halo planes,
+    // the pipeline fill and drain and the block's start cost as much as about
+    // eight planes (fitted to timings of 192^3 to 384^3 domains).  Take the
+    // tile and chunking with the least rounds x (chunk + 8) x plane time, the
+    // fewest chunks among equals.  Chunks shorter than 16 planes spend too much
+    // on their halo, unless the domain would then give fewer than two such
+    // tiles per CU: a small domain would leave most CUs idle, and its halo
+    // re-reads are L2 hits.
+    //
+    // The pair sweep takes any tile of up to 512 cells.  Its plane time falls
+    // by 30 % at most with the lanes that have a cell, rises with shorter rows
+    // (8 / w), and in domains many times the caches' size by 8 % for rows that
+    // split cache lines or fewer than eight of 64 (fitted to 20 domains in FP16
+    // and FP32, some 26 tiles and chunks each: 1 % off the best on average).
+    // Even parts of the domain are tried beside 64 x 8: 131^3 in FP16 takes 44 x 11
+    // tiles (108 us a step, 136 with 64 x 8), 100^3 50 x 9 (48 / 65), 72^3 in FP32
+    // 36 x 11 (29 / 42); 192^3 and 224^3 keep 64 x 8 (271 against 277 us with 64 x 7,
+    // 429 against 516 with 56 x 9 in FP16).
+    //
+    // In a batched launch every block strides over many tiles: there the tile of
+    // the least columns x plane time is taken, with 60 % of the time following
+    // the lanes in FP32, where enough tiles fill the memory (eight 96^3 domains:
+    // 501 us a step with 64 x 8 tiles, 523 with 48 x 10; twelve 67^3 431 and 312
+    // with 34 x 14; in FP16 317 and 299, 276 and 188).
+    double best = -1.0, batch_best = -1.0;
+    l.batch_x = 64;
+    l.batch_y = 8;
+    auto consider = [&](int w, int h) {
+        const int64_t cols = static_cast<int64_t>((p.nx + w - 1) / w) * ((p.ny + h - 1) / h);
+        const double lanes = static_cast<double>(p.nx) * p.ny / (static_cast<double>(cols) * (pair ? 512 : w * h));
+        const double lines = h * w == 512 && w % 32 == 0 ? 1.0 : 1.08;
+        const double plane = pair ? (0.7 + 0.3 * lanes) * (1.0 + 8.0 / w) * (p.N > 6000000 ? lines : 1.0) : 1.0;
+        const double share = p.storage == hm::kF32 ? 0.6 : 0.3;
+        const double column = static_cast<double>(cols) * (1.0 - share + share * lanes) * (1.0 + 8.0 / w) * lines;
+        if (pair && (batch_best < 0.0 || column < batch_best)) {
+            batch_best = column;
+            l.batch_x = w;
+            l.batch_y = h;
+        }
         const int64_t tiles16 = cols * ((p.nz + 15) / 16);
         const int64_t min_chunk = tiles16 >= 2 * ncu ? 16 : 4;
-        int64_t best_cost = -1;
         for (int64_t c = 1; c <= p.nz; ++c) {
-            const int64_t z = (p.nz + c - 1) / c;
-            if (c > 1 && z < min_chunk) break;
+            int64_t z = (p.nz + c - 1) / c;
+            if (c > 1 && z < min_chunk && !env_z) break;
+            if (env_z) z = std::min(std::max(env_z, 1), p.nz);
             const int64_t blocks = cols * ((p.nz + z - 1) / z);
-            const int64_t cost = ((blocks + ncu - 1) / ncu) * (z + 8);
-            if (best_cost < 0 || cost < best_cost) {
-                best_cost = cost;
-                zc = static_cast<int>(z);
+            const double cost = static_cast<double>(((blocks + ncu - 1) / ncu) * (z + 8)) * plane;
+            if (best < 0.0 || cost < best) {
+                best = cost;
+                l.tile_x = w;
+                l.tile_y = h;
+                l.zchunk = static_cast<int>(z);
+            }
+            if (env_z) break;
+        }
+    };
+    if (pair && !env_x && !env_y && p.nz > 1) {
+        auto part = [](int n, int k) { return (n + k - 1) / k; };
+        const int k0 = part(p.nx, 64);
+        for (int k = k0 - 1; k <= k0 + 3; ++k) {
+            const int w = k < k0 ? 64 : part(p.nx, k);
+            if (w > p.nx || (k > k0 && w < 24)) continue;
+            int h = part(p.ny, part(p.ny, std::min(std::min(16, 512 / w), p.ny)));
+            for (;;) {
+                consider(w, h);
+                if (h == 1 || h * w < 256) break;
+                h = part(p.ny, part(p.ny, h - 1));
             }
         }
     }
-    l.zchunk = std::min(std::max(zc, 1), p.nz);
+    if (best < 0.0) consider(l.tile_x, l.tile_y);
+    // Non-temporal stores keep the written state out of the caches' way, but
+    // where a tile's rows start or end inside a 128-byte line the two tiles that
+    // share it each write part of it, and only a cached line is merged before it
+    // goes out: 131^3 in FP32 169 us a step with cached stores against 205, 100^3 in
+    // FP16 48 against 56; with whole lines non-temporal stores are the faster ones
+    // (256^3 in FP32 970 against 997).
+    l.nt_stores = l.tile_x * word % 128 == 0 && p.nx * word % 128 == 0;
     return l;
 }
 
