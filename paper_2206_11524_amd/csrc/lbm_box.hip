@@ -15,7 +15,6 @@
 #include "lbm_device.h"
 
 #include <algorithm>
-#include <vector>
 
 namespace hm {
 
@@ -284,17 +283,13 @@ bool choose_box(const Problem& p, int cus, int* bx, int* by, int* bz)
     const int64_t ncu = std::max(cus, 1);
     double best = -1.0;
     auto part = [](int n, int k) { return (n + k - 1) / k; };
-    // the distinct sizes up to `most` that k even parts of n have
-    auto sizes = [&](int n, int most) {
-        std::vector<int> v;
-        for (int x = part(n, part(n, std::min(n, most))); x > 1; x = part(n, part(n, x - 1))) v.push_back(x);
-        v.push_back(1);
-        return v;
-    };
-    const std::vector<int> xs = sizes(p.nx, 128), ys = sizes(p.ny, 32), zs = sizes(p.nz, 32);
-    for (int x : xs)
-        for (int y : ys)
-            for (int z : zs) {
+    // the sizes that k even parts of n have, largest first, and the next one
+    auto first = [&](int n, int most) { return part(n, part(n, std::min(n, most))); };
+    auto next = [&](int n, int v) { return v > 1 ? part(n, part(n, v - 1)) : 0; };
+    const int least_x = std::min(p.nx, 8);  // shorter rows never win
+    for (int x = first(p.nx, 128); x >= least_x; x = next(p.nx, x))
+        for (int y = first(p.ny, 32); y; y = next(p.ny, y))
+            for (int z = first(p.nz, 32); z; z = next(p.nz, z)) {
                 if (!box_fits(p, x, y, z)) continue;
                 const int64_t blocks = static_cast<int64_t>(part(p.nx, x)) * part(p.ny, y) * part(p.nz, z);
                 const int waves = box_groups(p) * (whole_waves(x * y * z) + whole_waves(box_halo(p, x, y, z)));

@@ -92,7 +92,7 @@ int env_int(const char* name, int dflt)
     return std::atoi(v);
 }
 
-hm::Launch choose_launch(const hm::Problem& p, int cus)
+hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
 {
     hm::Launch l{};
     // small domains: the box kernel, unless a tile or chunk of the sweep is
@@ -103,7 +103,7 @@ hm::Launch choose_launch(const hm::Problem& p, int cus)
         if (std::sscanf(box, "%d,%d,%d", d, d + 1, d + 2) == 3 && hm::box_fits(p, d[0], d[1], d[2])) {
             l.bx = d[0]; l.by = d[1]; l.bz = d[2];
         }
-    } else if (!env_int("LBM_TILE_X", 0) && !env_int("LBM_TILE_Y", 0) && !env_int("LBM_ZCHUNK", 0) &&
+    } else if (!batched && !env_int("LBM_TILE_X", 0) && !env_int("LBM_TILE_Y", 0) && !env_int("LBM_ZCHUNK", 0) &&
                !hm::choose_box(p, cus, &l.bx, &l.by, &l.bz)) {
         l.bx = 0;
     }
@@ -124,6 +124,7 @@ hm::Launch choose_launch(const hm::Problem& p, int cus)
     }
     const int64_t ncu = std::max(cus, 1);
     const int64_t word = 2 * hm::storage_bytes(p.storage);
+    auto part = [](int n, int k) { return (n + k - 1) / k; };
     // One block fits a CU (registers and LDS), so blocks run in rounds of one
     // per CU, and a block takes about (chunk + 8) plane times: the halo planes,
     // the pipeline fill and drain and the block's start cost as much as about
@@ -164,25 +165,25 @@ hm::Launch choose_launch(const hm::Problem& p, int cus)
             l.batch_x = w;
             l.batch_y = h;
         }
+        if (batched) return;
         const int64_t tiles16 = cols * ((p.nz + 15) / 16);
-        const int64_t min_chunk = tiles16 >= 2 * ncu ? 16 : 4;
-        for (int64_t c = 1; c <= p.nz; ++c) {
-            int64_t z = (p.nz + c - 1) / c;
-            if (c > 1 && z < min_chunk && !env_z) break;
-            if (env_z) z = std::min(std::max(env_z, 1), p.nz);
-            const int64_t blocks = cols * ((p.nz + z - 1) / z);
+        const int min_chunk = tiles16 >= 2 * ncu ? 16 : 4;
+        // the distinct chunk lengths of even parts of nz, longest first
+        for (int z = env_z ? std::min(std::max(env_z, 1), p.nz) : p.nz;;) {
+            const int64_t blocks = cols * part(p.nz, z);
             const double cost = static_cast<double>(((blocks + ncu - 1) / ncu) * (z + 8)) * plane;
             if (best < 0.0 || cost < best) {
                 best = cost;
                 l.tile_x = w;
                 l.tile_y = h;
-                l.zchunk = static_cast<int>(z);
+                l.zchunk = z;
             }
-            if (env_z) break;
+            if (env_z || z == 1) break;
+            z = part(p.nz, part(p.nz, z - 1));
+            if (z < min_chunk) break;
         }
     };
     if (pair && !env_x && !env_y && p.nz > 1) {
-        auto part = [](int n, int k) { return (n + k - 1) / k; };
         const int k0 = part(p.nx, 64);
         for (int k = k0 - 1; k <= k0 + 3; ++k) {
             const int w = k < k0 ? 64 : part(p.nx, k);
@@ -195,7 +196,7 @@ hm::Launch choose_launch(const hm::Problem& p, int cus)
             }
         }
     }
-    if (best < 0.0) consider(l.tile_x, l.tile_y);
+    if (best < 0.0) consider(l.tile_x, l.tile_y);  // one tile in the split layout, or as given
     // Non-temporal stores keep the written state out of the caches' way, but
     // where a tile's rows start or end inside a 128-byte line the two tiles that
     // share it each write part of it, and only a cached line is merged before it
@@ -327,7 +328,7 @@ int lbm_create(const lbm_domain* dom, const float* n_s, const double* rho_init, 
         delete c;
         return LBM_EDEVICE;
     }
-    c->launch = choose_launch(c->prob, cus);
+    c->launch = choose_launch(c->prob, cus, false);
     if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess) {
         lbm_destroy(c);
         return LBM_EDEVICE;
@@ -397,7 +398,7 @@ int hm_rt::ctx_bind(const lbm_domain* dom, const lbm_params* prm, const lbm_devi
         lbm_destroy(c);
         return LBM_EDEVICE;
     }
-    c->launch = choose_launch(c->prob, cus);
+    c->launch = choose_launch(c->prob, cus, true);
     *out = c;
     return LBM_OK;
 }
