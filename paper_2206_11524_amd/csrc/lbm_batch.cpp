@@ -37,14 +37,13 @@ class BatchRunner {
   public:
     ~BatchRunner() { release(); }
 
-    // tile_x, tile_y: tile of every domain, 0: the pair layout takes each
-    // domain's own (Launch::batch_x, batch_y), the split layout 64 x 8.  nt: the
-    // store policy whose graphs are captured now (the other's when a tick needs
-    // them).
+    // tile_x, tile_y: tile of every domain that can take it, 0: each domain's own
+    // (Launch::batch_x, batch_y).  nt: the store policy whose graphs are captured
+    // now (the other's when a tick needs them).
     int init(int storage, int ncomp, int c_ns, int tile_x, int tile_y, int max_domains, int k_graph, bool nt,
              hipStream_t st)
     {
-        own_tiles_ = !tile_x && !tile_y && hm::pair_layout(storage, ncomp);
+        own_tiles_ = !tile_x && !tile_y;
         if (!tile_x) tile_x = 64;
         if (!tile_y) tile_y = 8;
         storage_ = storage;
@@ -62,7 +61,7 @@ class BatchRunner {
         // every block resident from the start: blocks stride over the tiles in
         // table order, so a block that had to wait for a CU would start its
         // whole share late
-        grid_ = std::max(8, cus * hm::batch_blocks_per_cu(storage, ncomp, c_ns, tile_x, tile_y));
+        grid_ = std::max(8, cus * hm::batch_blocks_per_cu(storage, ncomp, c_ns));
         cus_ = std::max(cus, 1);
         tpc_ = std::max(0, hm_rt::env_int("LBM_BATCH_TILES_PER_CU", 0));  // 0: planned per launch
         maxc_ = std::max(4, hm_rt::env_int("LBM_BATCH_MAX_CHUNK", 64));
@@ -94,7 +93,7 @@ class BatchRunner {
             }
             bool ok = true;
             for (int k = 0; k < kmax_; ++k)
-                ok = ok && hm::launch_step_batch(storage_, ncomp_, c_ns_, tx_, ty_, dev_[j], k, grid_, nt, stream_) ==
+                ok = ok && hm::launch_step_batch(storage_, ncomp_, c_ns_, dev_[j], k, grid_, nt, stream_) ==
                                hipSuccess;
             if (hipStreamEndCapture(stream_, &g) != hipSuccess || !ok || !g) {
                 graphs_ok_ = false;
@@ -112,8 +111,9 @@ class BatchRunner {
     // stores; otherwise the rows' shared lines are merged in the caches.
     static bool whole_lines(const hm::BatchDomain& d)
     {
-        if (!hm::pair_layout(d.prob.storage, d.prob.ncomp)) return true;  // one policy
-        const int64_t word = 2 * hm::storage_bytes(d.prob.storage);
+        if (d.prob.storage == hm::kF64) return true;  // one policy
+        const int64_t word =
+            hm::storage_bytes(d.prob.storage) * (hm::pair_layout(d.prob.storage, d.prob.ncomp) ? 2 : 1);
         return d.tile_x * word % 128 == 0 && d.prob.nx * word % 128 == 0;
     }
 
@@ -132,7 +132,7 @@ class BatchRunner {
         int64_t cols = 0, tiles16 = 0;
         bool nt = true;
         for (hm::BatchDomain& b : balanced_) {
-            if (!own_tiles_) {
+            if (!own_tiles_ && hm::tile_supported(b.prob, tx_, ty_)) {
                 b.tile_x = tx_;
                 b.tile_y = ty_;
             }
@@ -169,7 +169,7 @@ class BatchRunner {
             HIP_TRY(hipGraphLaunch(exec_[nt ? 1 : 0][j], stream_));
         } else {
             for (int kk = 0; kk < k; ++kk)
-                HIP_TRY(hm::launch_step_batch(storage_, ncomp_, c_ns_, tx_, ty_, dev_[j], kk, grid_, nt, stream_));
+                HIP_TRY(hm::launch_step_batch(storage_, ncomp_, c_ns_, dev_[j], kk, grid_, nt, stream_));
         }
         HIP_TRY(hipEventRecord(t1_, stream_));
         last_k_ = k;

@@ -30,17 +30,6 @@ struct BoxDims {
     int own_pad, halo_pad;
 };
 
-template <typename V>
-__device__ __forceinline__ void box_store(V v, rsrc_t r, uint32_t vo, uint32_t so)
-{
-    if constexpr (sizeof(V) == 8)
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, vo, so, kNT);
-    else if constexpr (sizeof(V) == 4)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, vo, so, kNT);
-    else
-        __builtin_amdgcn_raw_buffer_store_b16(v, r, vo, so, kNT);
-}
-
 template <typename ST, int NC, int CNS, bool PAIR>
 struct BoxShared {
     using T = typename ST::T;
@@ -178,7 +167,7 @@ __global__ __launch_bounds__(kBoxMaxThreads) void k_step_box(Args<typename ST::T
         pair_collide<ST, CNS, FS, RND>(
             geo, a, rbits, t_key, cell, me, rho0 - lxy, rho0, rho0 + lxy, ns0 - lxy, ns0, ns0 + lxy, jm,
             [&](int i) { return e[i]; },
-            [&](int i, W v) { box_store(v, rb, own, static_cast<uint32_t>(i) * dir_bytes); });
+            [&](int i, W v) { raw_store<kNT>(v, rb, own, static_cast<uint32_t>(i) * dir_bytes); });
     } else {
         T h[kQ];
         if (act) {
@@ -217,7 +206,7 @@ __global__ __launch_bounds__(kBoxMaxThreads) void k_step_box(Args<typename ST::T
         const rsrc_t rb = make_rsrc(reinterpret_cast<W*>(B) + s * cstride, all_bytes);
         split_collide<ST, NC, CNS, FS>(
             geo, a, s, t_key, cell, me, rho0 - lxy, rho0, rho0 + lxy, ns0 - lxy, ns0, ns0 + lxy, jc, h,
-            [&](int i, W v) { box_store(v, rb, own, static_cast<uint32_t>(i) * dir_bytes); });
+            [&](int i, W v) { raw_store<kNT>(v, rb, own, static_cast<uint32_t>(i) * dir_bytes); });
     }
 }
 

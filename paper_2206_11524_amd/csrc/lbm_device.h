@@ -57,10 +57,6 @@ struct F64 {
     {
         return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0));
     }
-    static __device__ __forceinline__ void bst(E v, rsrc_t r, uint32_t vo, uint32_t so)
-    {
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, vo, so, kNT);
-    }
 };
 struct F32 {
     using E = float;
@@ -72,19 +68,11 @@ struct F32 {
     {
         return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
     }
-    static __device__ __forceinline__ void bst(E v, rsrc_t r, uint32_t vo, uint32_t so)
-    {
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, vo, so, kNT);
-    }
 };
 struct Half16 {
     static __device__ __forceinline__ uint16_t bld(rsrc_t r, uint32_t vo, uint32_t so)
     {
         return __builtin_amdgcn_raw_buffer_load_b16(r, vo, so, 0);
-    }
-    static __device__ __forceinline__ void bst(uint16_t v, rsrc_t r, uint32_t vo, uint32_t so)
-    {
-        __builtin_amdgcn_raw_buffer_store_b16(v, r, vo, so, kNT);
     }
 };
 struct F16 : Half16 {
@@ -272,11 +260,25 @@ __device__ __forceinline__ W word_load(rsrc_t r, uint32_t vo, uint32_t so)
     else return __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0);
 }
 
-template <typename W, int AUX>
-__device__ __forceinline__ void word_store(W v, rsrc_t r, uint32_t vo, uint32_t so)
+// store of one stored value or word of 2, 4 or 8 bytes with cache policy AUX
+template <int AUX, typename V>
+__device__ __forceinline__ void raw_store(V v, rsrc_t r, uint32_t vo, uint32_t so)
 {
-    if constexpr (sizeof(W) == 8) __builtin_amdgcn_raw_buffer_store_b64(v, r, vo, so, AUX);
-    else __builtin_amdgcn_raw_buffer_store_b32(v, r, vo, so, AUX);
+    if constexpr (sizeof(V) == 8)
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, vo, so, AUX);
+    else if constexpr (sizeof(V) == 4)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, vo, so, AUX);
+    else
+        __builtin_amdgcn_raw_buffer_store_b16(v, r, vo, so, AUX);
+}
+
+// Bounds of the split sweep's tiles: cells (a thread per cell and component) and
+// rows.  FP64 with two components takes half the cells to stay within the
+// register file without spills.
+constexpr int split_cells(bool f64, int ncomp) { return f64 && ncomp == 2 ? 256 : 512; }
+constexpr int split_rows(bool f64, int ncomp, int c_ns)
+{
+    return ncomp == 1 ? 16 : (f64 ? 5 : (c_ns == 1 ? 10 : 8));
 }
 
 // Kernel parameters in the arithmetic type.
@@ -287,7 +289,7 @@ struct Args {
     int64_t N;   // cells
     int pair;    // populations in the pair layout
     int zchunk, ntx, nty, nzc;
-    int tw, th;  // tile of the pair sweep
+    int tw, th;  // tile of the sweep
     T inv_tau[2], tau[2];
     T G_s, Gads_s[2];
     T F[3];
@@ -446,6 +448,14 @@ __device__ __forceinline__ int xcd_tile(int b, int nb)
 {
     const int k = b & 7, q = nb >> 3, r = nb & 7;
     return k * q + min(k, r) + (b >> 3);
+}
+
+// The same for sweeps whose blocks run in rounds of `resident`: the runs are
+// those of each round, so that one round covers one stretch of the domain.
+__device__ __forceinline__ int xcd_tile(int b, int nb, int resident)
+{
+    const int base = b / resident * resident;
+    return base + xcd_tile(b - base, min(resident, nb - base));
 }
 
 __device__ __forceinline__ int wrap_dec(int v, int n) { return v == 0 ? n - 1 : v - 1; }

@@ -36,12 +36,12 @@ struct Problem {
 };
 
 struct Launch {
-    int tile_x;   // cells per tile row and rows per tile: 128 x 4, 64 x 4 or 8, 32 x 4, 8 or 16
-    int tile_y;   // in the split layout; any up to 64 x 16 of at most 512 cells in the pair layout
+    int tile_x;   // cells per tile row (up to 64)
+    int tile_y;   // rows per tile, within tile_limits
     int zchunk;   // planes per block
-    bool nt_stores;  // pair layout: non-temporal stores
+    bool nt_stores;  // non-temporal stores (always in FP64)
     int bx, by, bz;  // cells per block of the box kernel (small domains); bx = 0: the sweep
-    int batch_x, batch_y;  // tile in a batched launch (pair layout)
+    int batch_x, batch_y;  // tile in a batched launch
 };
 
 // True if two components in this format use the pair layout: both values of
@@ -50,9 +50,10 @@ struct Launch {
 // runs use the split layout [s][z][i][y][x].
 bool pair_layout(int storage, int ncomp, int forcing = kForcingShanChen);
 
-// True if the tile shape is compiled in for this format, component count and
-// forcing scheme.
-bool tile_supported(int storage, int ncomp, int tile_x, int tile_y, int forcing = kForcingShanChen);
+// Most cells and rows of a tile of the sweep that runs the problem, and whether
+// a tile keeps to them.
+void tile_limits(const Problem& p, int* cells, int* rows);
+bool tile_supported(const Problem& p, int tile_x, int tile_y);
 
 // Bytes per stored population.
 int storage_bytes(int storage);
@@ -154,14 +155,13 @@ bool batch_tile_supported(int storage, int ncomp, int tile_x, int tile_y);
 
 // Blocks of the batched kernel that fit one CU at once (registers, LDS); at
 // least 1.
-int batch_blocks_per_cu(int storage, int ncomp, int c_ns, int tile_x, int tile_y);
+int batch_blocks_per_cu(int storage, int ncomp, int c_ns);
 
 // Launch k of a tick: every domain with k < steps takes one step.  The grid
-// strides over all tiles of the table, so any fixed grid size works.  In the
-// split layout every domain has the tile tile_x x tile_y; nt: non-temporal
-// stores (pair layout).
-hipError_t launch_step_batch(int storage, int ncomp, int c_ns, int tile_x, int tile_y, const void* table, int k,
-                             int grid, bool nt, hipStream_t st);
+// strides over all tiles of the table, so any fixed grid size works.  nt:
+// non-temporal stores (always in FP64).
+hipError_t launch_step_batch(int storage, int ncomp, int c_ns, const void* table, int k, int grid, bool nt,
+                             hipStream_t st);
 
 // Convergence monitor (server): one domain of a monitor table.
 struct MonitorDomain {

@@ -15,7 +15,7 @@
 // partial bounce-back blend because w_ibar = w_i), which keeps small deviations
 // representable in reduced precision.
 //
-// The step kernels are fused 2.5-D sweeps: a block owns a TX x TY column of
+// The step kernels are fused 2.5-D sweeps: a block owns a column of w x h
 // cells and marches along z.  For every plane it pulls the populations of its
 // cells once (kept for the collision of a later iteration), forms the
 // densities, and stages them in LDS together with a one-cell ring of densities
@@ -32,8 +32,8 @@
 
 namespace hm {
 
-// One thread per (cell, component): a block of NC*TX*TY threads owns a TX x TY
-// column of cells; threads [s*TX*TY, (s+1)*TX*TY) handle component s.  The two
+// One thread per (cell, component): a block of NC*kCells threads owns a column of
+// w x h cells; threads [s*kCells, (s+1)*kCells) handle component s.  The two
 // components of a cell meet only through LDS (densities and first moments),
 // which halves the registers per thread and doubles the waves per CU.
 //
@@ -42,39 +42,43 @@ namespace hm {
 // runs ahead into staging plane z+2 writes slots that no wave still colliding
 // plane z reads, and every wave has left the collision of plane z-1 before the
 // barrier that precedes the collision of plane z.
-template <typename ST, int NC, int CNS, int TX, int TY>
+//
+// A tile is any w x h cells of at most kCells with rows of up to 64 and at most
+// kRows rows, fitted to the domain like the pair sweep's (the row bound keeps the
+// staged planes within the 160 KB of LDS; lanes take the cells row by row).
+template <typename ST, int NC, int CNS>
 struct TileShared {
     using T = typename ST::T;
-    static constexpr int LW = TX + 2;
-    static constexpr int LP = LW * (TY + 2);
-    static constexpr int NTC = TX * TY;
+    static constexpr int kCells = split_cells(sizeof(T) == 8, NC);
+    static constexpr int kRows = split_rows(sizeof(T) == 8, NC, CNS);
+    static constexpr int kStaged = 66 * (kCells / 64 + 2);  // cells of a tile with its ring, at most
+    static constexpr int LW = 66;
+    static constexpr int LP = LW * (kRows + 2);
+    static constexpr int NTC = kCells;
     static constexpr int NT = NC * NTC;
-    // Where the tile fits the 160 KB of LDS with it: the populations of the
-    // plane staged last wait here (private to each thread) until it is
-    // collided, which frees the registers that keep the next plane's loads
-    // in flight (the three-plane sweep of step_tile)
-    static constexpr size_t kBase = sizeof(T) * (4 * NC * LP + 3 * NC * 3 * NTC) + sizeof(float) * 4 * CNS * LP;
-    static constexpr bool kPipe = kBase + sizeof(T) * kQ * NT <= 160 * 1024;
+    // the populations of the plane staged last wait here (private to each
+    // thread) until it is collided, which frees the registers that keep the
+    // next plane's loads in flight
+    T hs[kQ][NT];
     T rho[4][NC][LP];
     float ns[4][CNS][LP];
-    T j[3][NC][3][NTC];
-    T hs[kPipe ? kQ : 1][kPipe ? NT : 1];
+    T j[NC == 2 ? 3 : 1][NC][3][NC == 2 ? NTC : 1];
 };
 
 // The sweep of one tile column (logical tile index L of the domain described
 // by a).  Shared by the single-domain and the batched kernels.
-template <typename ST, int NC, int CNS, int TX, int TY, int FS, bool ONE = false>
+template <typename ST, int NC, int CNS, int FS, bool ONE, int AUX>
 __device__ __forceinline__ void step_tile(const Args<typename ST::T>& a, const typename ST::E* __restrict__ A,
                                           typename ST::E* __restrict__ B, const float* __restrict__ ns, int L,
-                                          uint32_t t, TileShared<ST, NC, CNS, TX, TY>& sh)
+                                          uint32_t t, TileShared<ST, NC, CNS>& sh)
 {
     using T = typename ST::T;
     using E = typename ST::E;
-    constexpr int LW = TX + 2;
-    constexpr int LP = LW * (TY + 2);
-    constexpr int NTC = TX * TY;  // threads per component
-    constexpr int NT = NC * NTC;
-    constexpr int NSMAX = (LP + NT - 1) / NT;  // n_s cells staged per thread and plane
+    using Shared = TileShared<ST, NC, CNS>;
+    constexpr int LW = Shared::LW, LP = Shared::LP;
+    constexpr int NTC = Shared::NTC;  // threads per component
+    constexpr int NT = Shared::NT;
+    constexpr int NSMAX = (Shared::kStaged + NT - 1) / NT;  // n_s cells staged per thread and plane
     auto& s_rho = sh.rho;
     auto& s_ns = sh.ns;
     auto& s_j = sh.j;
@@ -82,11 +86,11 @@ __device__ __forceinline__ void step_tile(const Args<typename ST::T>& a, const t
     const int tx = L % a.ntx;
     const int ty = (L / a.ntx) % a.nty;
     const int tz = L / (a.ntx * a.nty);
-    const int x0 = tx * TX, y0 = ty * TY;
+    const int x0 = tx * a.tw, y0 = ty * a.th;
     const int zs = tz * a.zchunk;
     const int ze = min(zs + a.zchunk, a.nz);
-    const int TXe = min(TX, a.nx - x0);
-    const int TYe = min(TY, a.ny - y0);
+    const int TXe = min(a.tw, a.nx - x0);
+    const int TYe = min(a.th, a.ny - y0);
     const int plane = a.nx * a.ny;
 
     // component of this thread; NTC is a multiple of 64, so it is the same
@@ -96,15 +100,12 @@ __device__ __forceinline__ void step_tile(const Args<typename ST::T>& a, const t
     const int s = NC == 1 ? 0 : __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / NTC);
     static_assert(NTC % 64 == 0, "a wave must not straddle two components");
     const int tl = static_cast<int>(threadIdx.x) - s * NTC;
-    const int lx = tl % TX;
-    const int ly = tl / TX;
-    const bool act = lx < TXe && ly < TYe;
-    const int x = x0 + min(lx, TXe - 1);
-    const int y = y0 + min(ly, TYe - 1);
-    // LDS cell and first-moment slot of the (clamped) own cell: a lane beyond
-    // a ragged tile edge duplicates the last active lane of its row/column
-    const int me = (y - y0 + 1) * LW + (x - x0 + 1);
-    const int tj = (y - y0) * TX + (x - x0);
+    // a lane beyond the last cell duplicates it
+    const int tj = min(tl, TXe * TYe - 1);  // cell of the tile, first-moment slot
+    const int ly = TXe == 64 ? tj >> 6 : tj / TXe;
+    const int x = x0 + (tj - ly * TXe);
+    const int y = y0 + ly;
+    const int me = (ly + 1) * LW + (x - x0 + 1);  // LDS cell
     const PlaneOffs qme = plane_offs<sizeof(E)>(x, y, a.nx, a.ny);
     const uint32_t own = static_cast<uint32_t>(y * a.nx + x) * static_cast<uint32_t>(sizeof(E));
 
@@ -157,10 +158,6 @@ __device__ __forceinline__ void step_tile(const Args<typename ST::T>& a, const t
         return make_rsrc(base + static_cast<size_t>(p) * kQ * static_cast<size_t>(plane), blk_bytes);
     };
 
-    auto pull_plane = [&](int p, const PlaneOffs& q, T h[kQ]) {
-        const rsrc_t r3[3] = {blk(Ac, wrapz(p + 1)), blk(Ac, p), blk(Ac, wrapz(p - 1))};  // c_z = -1, 0, +1
-        pull<ST, T>(r3, dir_bytes, q, a.inv_scale, h);
-    };
     // A select per value rather than a per-lane branch: in divergent control
     // flow a branch makes the compiler merge the two versions of all 19
     // values through copies, doubling the registers they hold.  The selects
@@ -175,41 +172,10 @@ __device__ __forceinline__ void step_tile(const Args<typename ST::T>& a, const t
         }
     };
 
-    // Stage plane p into LDS slot `slot`: densities of the own cell and of
-    // the ring cell, first moments of the own cell (slot js, none if js < 0),
-    // n_s; the own cell's populations stay in h for the collision.
-    auto stage_plane = [&](int p, int slot, int js, T h[kQ]) {
-        // issue the own and the ring loads before either is consumed, so a
-        // ring lane waits for one memory round trip per plane, not two
-        T hr[kQ];
-        if (act) pull_plane(p, qme, h);
-        if (ring) pull_plane(p, qring, hr);
-        if (act) {
-            reservoir_override(x, y, p, h);
-            s_rho[slot][s][me] = a.rho0[s] + sum19(h);
-            if (NC == 2 && js >= 0) {
-                s_j[js][s][0][tj] = first_moment<T, 0>(h);
-                s_j[js][s][1][tj] = first_moment<T, 1>(h);
-                s_j[js][s][2][tj] = first_moment<T, 2>(h);
-            }
-        }
-        if (ring) {
-            reservoir_override(rx, ry, p, hr);
-            s_rho[slot][s][rme] = a.rho0[s] + sum19(hr);
-        }
-        const float* nsp = ns + static_cast<size_t>(p) * plane;
-#pragma unroll
-        for (int k = 0; k < NSMAX; ++k)
-            if (ns_lds[k] >= 0)
-#pragma unroll
-                for (int c = 0; c < CNS; ++c) s_ns[slot][c][ns_lds[k]] = nsp[static_cast<size_t>(c) * a.N + ns_off[k]];
-    };
-
     // Collision of plane z of this thread's component from h (pre-collision,
     // shifted) and the LDS slots of planes z-1, z, z+1.
     const TileGeom<LW, LP> geo;
-    auto collide = [&](int z, int sm, int s0, int sp, int js, const T h[kQ], bool guard) {
-        if (guard && !act) return;
+    auto collide = [&](int z, int sm, int s0, int sp, int js, const T h[kQ]) {
         T jc[NC][3];
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
@@ -228,7 +194,7 @@ __device__ __forceinline__ void step_tile(const Args<typename ST::T>& a, const t
         split_collide<ST, NC, CNS, FS>(
             geo, a, s, t_key, cell, me, &s_rho[sm][0][0], &s_rho[s0][0][0], &s_rho[sp][0][0], &s_ns[sm][0][0],
             &s_ns[s0][0][0], &s_ns[sp][0][0], jc, h,
-            [&](int i, E v) { ST::bst(v, rz, own, static_cast<uint32_t>(i) * dir_bytes); });
+            [&](int i, E v) { raw_store<AUX>(v, rz, own, static_cast<uint32_t>(i) * dir_bytes); });
     };
 
     // plane p (zs-1 <= p <= ze) uses density slot (p - zs + 1) mod 4 and
@@ -236,226 +202,205 @@ __device__ __forceinline__ void step_tile(const Args<typename ST::T>& a, const t
     auto rslot = [&](int p) { return (p - zs + 1) & 3; };
     auto jslot = [&](int p) { return (p - zs) % 3; };
 
-    if constexpr (TileShared<ST, NC, CNS, TX, TY>::kPipe) {
-        // Three planes at a time: plane z is collided from registers, plane
-        // z+1 waits in LDS (hs), and the own loads of plane z+2 are in flight
-        // over the barrier and the collision of plane z.
-        //
-        // The compiler counts outstanding memory operations per control-flow
-        // path, and after a branch that may have skipped some it has to wait
-        // as if they had been issued last; a load or store under a per-lane
-        // condition would therefore make every later wait drain the loads
-        // kept in flight.  So nothing here touches memory conditionally:
-        // lanes beyond a ragged tile edge duplicate an active lane (same
-        // cell, same LDS slots, identical values written twice), lanes
-        // without a ring cell load the tile's last ring cell (a cell of the
-        // domain; the values are not used), and lanes without an n_s cell
-        // duplicate cell 0 of the staging list.
-        constexpr int NT_ = TileShared<ST, NC, CNS, TX, TY>::NT;
-        T* hs = &sh.hs[0][0] + threadIdx.x;
-        const PlaneOffs& qr = qring;
-        // list cell 0 is the corner (x0 - 1, y0 - 1), LDS index 0
-        const int ns_off0 = (((y0 - 1) % a.ny + a.ny) % a.ny) * a.nx + ((x0 - 1) % a.nx + a.nx) % a.nx;
-        int nl[NSMAX], no[NSMAX];
+    // Three planes at a time: plane z is collided from registers, plane
+    // z+1 waits in LDS (hs), and the own loads of plane z+2 are in flight
+    // over the barrier and the collision of plane z.
+    //
+    // The compiler counts outstanding memory operations per control-flow
+    // path, and after a branch that may have skipped some it has to wait
+    // as if they had been issued last; a load or store under a per-lane
+    // condition would therefore make every later wait drain the loads
+    // kept in flight.  So nothing here touches memory conditionally:
+    // lanes beyond a ragged tile edge duplicate an active lane (same
+    // cell, same LDS slots, identical values written twice), lanes
+    // without a ring cell load the tile's last ring cell (a cell of the
+    // domain; the values are not used), and lanes without an n_s cell
+    // duplicate cell 0 of the staging list.
+    T* hs = &sh.hs[0][0] + threadIdx.x;
+    const PlaneOffs& qr = qring;
+    // list cell 0 is the corner (x0 - 1, y0 - 1), LDS index 0
+    const int ns_off0 = (((y0 - 1) % a.ny + a.ny) % a.ny) * a.nx + ((x0 - 1) % a.nx + a.nx) % a.nx;
+    int nl[NSMAX], no[NSMAX];
 #pragma unroll
-        for (int k = 0; k < NSMAX; ++k) {
-            nl[k] = ns_lds[k] >= 0 ? ns_lds[k] : 0;
-            no[k] = ns_lds[k] >= 0 ? ns_off[k] : ns_off0;
+    for (int k = 0; k < NSMAX; ++k) {
+        nl[k] = ns_lds[k] >= 0 ? ns_lds[k] : 0;
+        no[k] = ns_lds[k] >= 0 ? ns_off[k] : ns_off0;
+    }
+    auto issue = [&](int p, const PlaneOffs& q, E e[kQ]) {
+        const rsrc_t r3[3] = {blk(Ac, wrapz(p + 1)), blk(Ac, p), blk(Ac, wrapz(p - 1))};
+        pull_raw<ST>(r3, dir_bytes, q, e);
+    };
+    if constexpr (ONE) {
+        // One cell deep (the instance launched for nz = 1): planes z - 1,
+        // z and z + 1 are all plane 0, so it is staged once and collided
+        // against itself (one memory round trip per step instead of the
+        // sweep's three; the three slots the sweep would fill hold the
+        // same values).  A kernel of its own: as a branch in the 3-D
+        // kernels it changed their register allocation.
+        const int slot = rslot(0), js = jslot(0);
+        E r1[kQ];
+        E r2[NC == 2 ? kQ : 1];
+        issue(0, qme, r1);
+        if constexpr (NC == 2) issue(0, qr, r2);
+        float nsv[NSMAX][CNS];
+#pragma unroll
+        for (int k = 0; k < NSMAX; ++k)
+#pragma unroll
+            for (int c = 0; c < CNS; ++c) nsv[k][c] = ns[static_cast<size_t>(c) * a.N + no[k]];
+        T h[kQ];
+#pragma unroll
+        for (int i = 0; i < kQ; ++i) h[i] = ST::dec(r1[i], a.inv_scale);
+        reservoir_override(x, y, 0, h);
+        s_rho[slot][s][me] = a.rho0[s] + sum19(h);
+        if constexpr (NC == 2) {
+            s_j[js][s][0][tj] = first_moment<T, 0>(h);
+            s_j[js][s][1][tj] = first_moment<T, 1>(h);
+            s_j[js][s][2][tj] = first_moment<T, 2>(h);
+            if (ring) {
+                T hr[kQ];
+#pragma unroll
+                for (int i = 0; i < kQ; ++i) hr[i] = ST::dec(r2[i], a.inv_scale);
+                reservoir_override(rx, ry, 0, hr);
+                s_rho[slot][s][rme] = a.rho0[s] + sum19(hr);
+            }
         }
-        auto issue = [&](int p, const PlaneOffs& q, E e[kQ]) {
-            const rsrc_t r3[3] = {blk(Ac, wrapz(p + 1)), blk(Ac, p), blk(Ac, wrapz(p - 1))};
-            pull_raw<ST>(r3, dir_bytes, q, e);
-        };
-        if constexpr (ONE) {
-            // One cell deep (the instance launched for nz = 1): planes z - 1,
-            // z and z + 1 are all plane 0, so it is staged once and collided
-            // against itself (one memory round trip per step instead of the
-            // sweep's three; the three slots the sweep would fill hold the
-            // same values).  A kernel of its own: as a branch in the 3-D
-            // kernels it changed their register allocation.
-            const int slot = rslot(0), js = jslot(0);
-            E r1[kQ];
-            E r2[NC == 2 ? kQ : 1];
-            issue(0, qme, r1);
-            if constexpr (NC == 2) issue(0, qr, r2);
+#pragma unroll
+        for (int k = 0; k < NSMAX; ++k)
+#pragma unroll
+            for (int c = 0; c < CNS; ++c) s_ns[slot][c][nl[k]] = nsv[k][c];
+        __syncthreads();
+        collide(0, slot, slot, slot, js, h);
+        return;
+    }
+    if constexpr (sizeof(E) == 8 || (sizeof(E) == 4 && FS == kForcingGuo)) {
+        E rr[kQ];  // own populations of the next plane to stage, raw
+        E er[kQ];  // ring populations of the plane being staged, raw
+        // Stage plane p, whose own loads are in rr: ring loads and n_s are
+        // issued first; the own values give the density and first moments
+        // and go to hs, whose previous content (the plane before) moves to
+        // hz; then the own loads of plane pn are issued, and only after them
+        // the ring values are consumed, so a wait for the ring does not wait
+        // for plane pn.
+        auto stage_pipe = [&](int p, int slot, int js, int pn, T hz[kQ]) {
+            if constexpr (NC == 2) issue(p, qr, er);
+            const float* nsp = ns + static_cast<size_t>(p) * plane;
             float nsv[NSMAX][CNS];
 #pragma unroll
             for (int k = 0; k < NSMAX; ++k)
 #pragma unroll
-                for (int c = 0; c < CNS; ++c) nsv[k][c] = ns[static_cast<size_t>(c) * a.N + no[k]];
-            T h[kQ];
+                for (int c = 0; c < CNS; ++c) nsv[k][c] = nsp[static_cast<size_t>(c) * a.N + no[k]];
+            __builtin_amdgcn_sched_barrier(0);
+            {
+                T h[kQ];
 #pragma unroll
-            for (int i = 0; i < kQ; ++i) h[i] = ST::dec(r1[i], a.inv_scale);
-            reservoir_override(x, y, 0, h);
-            s_rho[slot][s][me] = a.rho0[s] + sum19(h);
-            if constexpr (NC == 2) {
-                s_j[js][s][0][tj] = first_moment<T, 0>(h);
-                s_j[js][s][1][tj] = first_moment<T, 1>(h);
-                s_j[js][s][2][tj] = first_moment<T, 2>(h);
-                if (ring) {
-                    T hr[kQ];
-#pragma unroll
-                    for (int i = 0; i < kQ; ++i) hr[i] = ST::dec(r2[i], a.inv_scale);
-                    reservoir_override(rx, ry, 0, hr);
-                    s_rho[slot][s][rme] = a.rho0[s] + sum19(hr);
+                for (int i = 0; i < kQ; ++i) h[i] = ST::dec(rr[i], a.inv_scale);
+                reservoir_override(x, y, p, h);
+                s_rho[slot][s][me] = a.rho0[s] + sum19(h);
+                if (NC == 2 && js >= 0) {
+                    s_j[js][s][0][tj] = first_moment<T, 0>(h);
+                    s_j[js][s][1][tj] = first_moment<T, 1>(h);
+                    s_j[js][s][2][tj] = first_moment<T, 2>(h);
                 }
+#pragma unroll
+                for (int i = 0; i < kQ; ++i) {
+                    hz[i] = hs[i * NT];
+                    hs[i * NT] = h[i];
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            issue(pn, qme, rr);
+            __builtin_amdgcn_sched_barrier(0);
+            if (ring) {
+                T hr[kQ];
+#pragma unroll
+                for (int i = 0; i < kQ; ++i) hr[i] = ST::dec(er[i], a.inv_scale);
+                reservoir_override(rx, ry, p, hr);
+                s_rho[slot][s][rme] = a.rho0[s] + sum19(hr);
             }
 #pragma unroll
             for (int k = 0; k < NSMAX; ++k)
 #pragma unroll
                 for (int c = 0; c < CNS; ++c) s_ns[slot][c][nl[k]] = nsv[k][c];
+        };
+
+        T hz[kQ];
+        // prologue: plane zs-1 (densities only), plane zs (to hs)
+        issue(wrapz(zs - 1), qme, rr);
+        stage_pipe(wrapz(zs - 1), rslot(zs - 1), -1, zs, hz);
+        stage_pipe(zs, rslot(zs), jslot(zs), wrapz(zs + 1), hz);
+        for (int z = zs; z < ze; ++z) {
+            // after the last plane the next loads repeat the one just staged (L2 hits)
+            const int pn = z + 2 <= ze ? wrapz(z + 2) : wrapz(z + 1);
+            stage_pipe(wrapz(z + 1), rslot(z + 1), jslot(z + 1), pn, hz);
             __syncthreads();
-            collide(0, slot, slot, slot, js, h, false);
-            return;
-        }
-        if constexpr (sizeof(E) == 8 || (sizeof(E) == 4 && FS == kForcingGuo)) {
-            E rr[kQ];  // own populations of the next plane to stage, raw
-            E er[kQ];  // ring populations of the plane being staged, raw
-            // Stage plane p, whose own loads are in rr: ring loads and n_s are
-            // issued first; the own values give the density and first moments
-            // and go to hs, whose previous content (the plane before) moves to
-            // hz; then the own loads of plane pn are issued, and only after them
-            // the ring values are consumed, so a wait for the ring does not wait
-            // for plane pn.
-            auto stage_pipe = [&](int p, int slot, int js, int pn, T hz[kQ]) {
-                if constexpr (NC == 2) issue(p, qr, er);
-                const float* nsp = ns + static_cast<size_t>(p) * plane;
-                float nsv[NSMAX][CNS];
-    #pragma unroll
-                for (int k = 0; k < NSMAX; ++k)
-    #pragma unroll
-                    for (int c = 0; c < CNS; ++c) nsv[k][c] = nsp[static_cast<size_t>(c) * a.N + no[k]];
-                __builtin_amdgcn_sched_barrier(0);
-                {
-                    T h[kQ];
-    #pragma unroll
-                    for (int i = 0; i < kQ; ++i) h[i] = ST::dec(rr[i], a.inv_scale);
-                    reservoir_override(x, y, p, h);
-                    s_rho[slot][s][me] = a.rho0[s] + sum19(h);
-                    if (NC == 2 && js >= 0) {
-                        s_j[js][s][0][tj] = first_moment<T, 0>(h);
-                        s_j[js][s][1][tj] = first_moment<T, 1>(h);
-                        s_j[js][s][2][tj] = first_moment<T, 2>(h);
-                    }
-    #pragma unroll
-                    for (int i = 0; i < kQ; ++i) {
-                        hz[i] = hs[i * NT_];
-                        hs[i * NT_] = h[i];
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                issue(pn, qme, rr);
-                __builtin_amdgcn_sched_barrier(0);
-                if (ring) {
-                    T hr[kQ];
-    #pragma unroll
-                    for (int i = 0; i < kQ; ++i) hr[i] = ST::dec(er[i], a.inv_scale);
-                    reservoir_override(rx, ry, p, hr);
-                    s_rho[slot][s][rme] = a.rho0[s] + sum19(hr);
-                }
-    #pragma unroll
-                for (int k = 0; k < NSMAX; ++k)
-    #pragma unroll
-                    for (int c = 0; c < CNS; ++c) s_ns[slot][c][nl[k]] = nsv[k][c];
-            };
-
-            T hz[kQ];
-            // prologue: plane zs-1 (densities only), plane zs (to hs)
-            issue(wrapz(zs - 1), qme, rr);
-            stage_pipe(wrapz(zs - 1), rslot(zs - 1), -1, zs, hz);
-            stage_pipe(zs, rslot(zs), jslot(zs), wrapz(zs + 1), hz);
-            for (int z = zs; z < ze; ++z) {
-                // after the last plane the next loads repeat the one just staged (L2 hits)
-                const int pn = z + 2 <= ze ? wrapz(z + 2) : wrapz(z + 1);
-                stage_pipe(wrapz(z + 1), rslot(z + 1), jslot(z + 1), pn, hz);
-                __syncthreads();
-                collide(z, rslot(z - 1), rslot(z), rslot(z + 1), jslot(z), hz, false);
-            }
-        } else {
-            // One component in FP32 or a 16-bit format (two components run
-            // the pair kernel): no ring, and in 16-bit two planes of own loads
-            // in flight (a wave has at most 63 memory operations outstanding,
-            // and the 16-bit loads carry half the bytes each; for FP32 the
-            // deeper prefetch did not pay).
-            static_assert(NC == 1, "two components in FP32 or 16-bit run the pair kernel");
-            constexpr bool DEEP = sizeof(E) == 2;
-            constexpr int AHEAD = DEEP ? 2 : 1;  // planes between issue and consumption
-            E rA[kQ];
-            E rB[DEEP ? kQ : 1];
-            // Stage plane p, whose own loads are in rc: the n_s loads are
-            // issued first; the own values give the density and go to hs,
-            // whose previous content (the plane before) moves to hz; then the
-            // own loads of plane pn are issued into rc.
-            auto stage_pipe = [&](int p, int slot, int pn, T hz[kQ], E rc[kQ]) {
-                const float* nsp = ns + static_cast<size_t>(p) * plane;
-                float nsv[NSMAX][CNS];
-#pragma unroll
-                for (int k = 0; k < NSMAX; ++k)
-#pragma unroll
-                    for (int c = 0; c < CNS; ++c) nsv[k][c] = nsp[static_cast<size_t>(c) * a.N + no[k]];
-                __builtin_amdgcn_sched_barrier(0);
-                {
-                    T h[kQ];
-#pragma unroll
-                    for (int i = 0; i < kQ; ++i) h[i] = ST::dec(rc[i], a.inv_scale);
-                    reservoir_override(x, y, p, h);
-                    s_rho[slot][s][me] = a.rho0[s] + sum19(h);
-#pragma unroll
-                    for (int i = 0; i < kQ; ++i) {
-                        hz[i] = hs[i * NT_];
-                        hs[i * NT_] = h[i];
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                issue(pn, qme, rc);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int k = 0; k < NSMAX; ++k)
-#pragma unroll
-                    for (int c = 0; c < CNS; ++c) s_ns[slot][c][nl[k]] = nsv[k][c];
-            };
-            // the plane whose loads a stage of plane p issues: p + AHEAD, or
-            // after the last plane one already staged again (L2 hits)
-            auto ahead = [&](int p) { return wrapz(p + AHEAD <= ze ? p + AHEAD : ze); };
-            // register sets: planes zs-1, zs+1, ... in r_odd, planes zs, zs+2, ...
-            // in r_even (one and the same set unless two planes are in flight)
-            E (&r_odd)[kQ] = rA;
-            E (&r_even)[kQ] = *reinterpret_cast<E(*)[kQ]>(DEEP ? static_cast<E*>(rB) : static_cast<E*>(rA));
-
-            T hz[kQ];
-            // prologue: planes zs-1 (densities only) and zs (to hs)
-            issue(wrapz(zs - 1), qme, r_odd);
-            if constexpr (DEEP) issue(zs, qme, r_even);
-            stage_pipe(wrapz(zs - 1), rslot(zs - 1), ahead(zs - 1), hz, r_odd);
-            stage_pipe(zs, rslot(zs), ahead(zs), hz, r_even);
-            // unrolled by two so the register sets keep fixed names
-            for (int z = zs; z < ze; z += 2) {
-                stage_pipe(wrapz(z + 1), rslot(z + 1), ahead(z + 1), hz, r_odd);
-                __syncthreads();
-                collide(z, rslot(z - 1), rslot(z), rslot(z + 1), jslot(z), hz, false);
-                if (z + 1 >= ze) break;
-                stage_pipe(wrapz(z + 2), rslot(z + 2), ahead(z + 2), hz, r_even);
-                __syncthreads();
-                collide(z + 1, rslot(z), rslot(z + 1), rslot(z + 2), jslot(z + 1), hz, false);
-            }
+            collide(z, rslot(z - 1), rslot(z), rslot(z + 1), jslot(z), hz);
         }
     } else {
-        T hA[kQ];
-        T hB[kQ];
+        // One component in FP32 or a 16-bit format (two components run
+        // the pair kernel): no ring, and in 16-bit two planes of own loads
+        // in flight (a wave has at most 63 memory operations outstanding,
+        // and the 16-bit loads carry half the bytes each; for FP32 the
+        // deeper prefetch did not pay).
+        static_assert(NC == 1, "two components in FP32 or 16-bit run the pair kernel");
+        constexpr bool DEEP = sizeof(E) == 2;
+        constexpr int AHEAD = DEEP ? 2 : 1;  // planes between issue and consumption
+        E rA[kQ];
+        E rB[DEEP ? kQ : 1];
+        // Stage plane p, whose own loads are in rc: the n_s loads are
+        // issued first; the own values give the density and go to hs,
+        // whose previous content (the plane before) moves to hz; then the
+        // own loads of plane pn are issued into rc.
+        auto stage_pipe = [&](int p, int slot, int pn, T hz[kQ], E rc[kQ]) {
+            const float* nsp = ns + static_cast<size_t>(p) * plane;
+            float nsv[NSMAX][CNS];
+#pragma unroll
+            for (int k = 0; k < NSMAX; ++k)
+#pragma unroll
+                for (int c = 0; c < CNS; ++c) nsv[k][c] = nsp[static_cast<size_t>(c) * a.N + no[k]];
+            __builtin_amdgcn_sched_barrier(0);
+            {
+                T h[kQ];
+#pragma unroll
+                for (int i = 0; i < kQ; ++i) h[i] = ST::dec(rc[i], a.inv_scale);
+                reservoir_override(x, y, p, h);
+                s_rho[slot][s][me] = a.rho0[s] + sum19(h);
+#pragma unroll
+                for (int i = 0; i < kQ; ++i) {
+                    hz[i] = hs[i * NT];
+                    hs[i * NT] = h[i];
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            issue(pn, qme, rc);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < NSMAX; ++k)
+#pragma unroll
+                for (int c = 0; c < CNS; ++c) s_ns[slot][c][nl[k]] = nsv[k][c];
+        };
+        // the plane whose loads a stage of plane p issues: p + AHEAD, or
+        // after the last plane one already staged again (L2 hits)
+        auto ahead = [&](int p) { return wrapz(p + AHEAD <= ze ? p + AHEAD : ze); };
+        // register sets: planes zs-1, zs+1, ... in r_odd, planes zs, zs+2, ...
+        // in r_even (one and the same set unless two planes are in flight)
+        E (&r_odd)[kQ] = rA;
+        E (&r_even)[kQ] = *reinterpret_cast<E(*)[kQ]>(DEEP ? static_cast<E*>(rB) : static_cast<E*>(rA));
 
-        // prologue: plane zs-1 (densities only), plane zs (kept in hA)
-        stage_plane(wrapz(zs - 1), rslot(zs - 1), -1, hB);
-        stage_plane(zs, rslot(zs), jslot(zs), hA);
-
-        // sweep, two planes per iteration so the register sets alternate roles
+        T hz[kQ];
+        // prologue: planes zs-1 (densities only) and zs (to hs)
+        issue(wrapz(zs - 1), qme, r_odd);
+        if constexpr (DEEP) issue(zs, qme, r_even);
+        stage_pipe(wrapz(zs - 1), rslot(zs - 1), ahead(zs - 1), hz, r_odd);
+        stage_pipe(zs, rslot(zs), ahead(zs), hz, r_even);
+        // unrolled by two so the register sets keep fixed names
         for (int z = zs; z < ze; z += 2) {
-            stage_plane(wrapz(z + 1), rslot(z + 1), jslot(z + 1), hB);
+            stage_pipe(wrapz(z + 1), rslot(z + 1), ahead(z + 1), hz, r_odd);
             __syncthreads();
-            collide(z, rslot(z - 1), rslot(z), rslot(z + 1), jslot(z), hA, true);
+            collide(z, rslot(z - 1), rslot(z), rslot(z + 1), jslot(z), hz);
             if (z + 1 >= ze) break;
-            stage_plane(wrapz(z + 2), rslot(z + 2), jslot(z + 2), hA);
+            stage_pipe(wrapz(z + 2), rslot(z + 2), ahead(z + 2), hz, r_even);
             __syncthreads();
-            collide(z + 1, rslot(z), rslot(z + 1), rslot(z + 2), jslot(z + 1), hB, true);
+            collide(z + 1, rslot(z), rslot(z + 1), rslot(z + 2), jslot(z + 1), hz);
         }
     }
 }
@@ -472,7 +417,7 @@ __device__ __forceinline__ void step_tile(const Args<typename ST::T>& a, const t
 // components of a cell meet in registers, so the first moments need no LDS
 // exchange; the densities still go to LDS for the force stencils.
 //
-// The waves of a block have fixed roles.  The first TX*TY threads own one
+// The waves of a block have fixed roles.  The first kPairCells threads own one
 // cell each: they pull, collide and store it, with the next plane's loads in
 // flight.  The last NR threads (whole waves) stage the one-cell ring of
 // densities around the tile and the n_s planes: they hold no collision state,
@@ -657,7 +602,7 @@ __device__ __forceinline__ void step_tile_pair(const Args<float>& a,
     // last cell duplicates it (same cell, same LDS slots, identical values
     // written twice)
     const int cq = min(tl, TXe * TYe - 1);
-    const int ly = cq / TXe;
+    const int ly = TXe == 64 ? cq >> 6 : cq / TXe;
     const int x = x0 + (cq - ly * TXe);
     const int y = y0 + ly;
     const int me = (y - y0 + 1) * LW + (x - x0 + 1);
@@ -675,7 +620,7 @@ __device__ __forceinline__ void step_tile_pair(const Args<float>& a,
         pair_collide<ST, CNS, FS, RND>(
             geo, a, cxy | reservoir_z_bits(a, z), t_key, cell, me, &s_rho[sm][0][0], &s_rho[s0][0][0], &s_rho[sp][0][0],
             &s_ns[sm][0][0], &s_ns[s0][0][0], &s_ns[sp][0][0], jm, wd,
-            [&](int i, W v) { word_store<W, AUX>(v, rz, own, static_cast<uint32_t>(i) * dir_bytes); });
+            [&](int i, W v) { raw_store<AUX>(v, rz, own, static_cast<uint32_t>(i) * dir_bytes); });
     };
 
     if constexpr (ONE) {
@@ -790,24 +735,27 @@ __device__ __forceinline__ void step_tile_pair(const Args<float>& a,
     }
 }
 
-template <typename ST, int NC, int TX, int TY, int FS = kForcingShanChen>
-constexpr int kThreads = kPair<ST, NC, FS> ? kPairCells + kPairRing : NC * TX * TY;
+template <typename ST, int NC, int FS = kForcingShanChen>
+constexpr int kThreads = kPair<ST, NC, FS> ? kPairCells + kPairRing : NC * split_cells(sizeof(typename ST::T) == 8, NC);
 
-template <typename ST, int NC, int CNS, int TX, int TY, int FS, bool ONE, int RND, int AUX>
-__global__ __launch_bounds__((kThreads<ST, NC, TX, TY, FS>)) void k_step(Args<typename ST::T> a,
+template <typename ST, int NC, int CNS, int FS, bool ONE, int RND, int AUX>
+__global__ __launch_bounds__((kThreads<ST, NC, FS>)) void k_step(Args<typename ST::T> a,
                                                                     const typename ST::E* __restrict__ A,
                                                                     typename ST::E* __restrict__ B,
                                                                     const float* __restrict__ ns)
 {
-    const int L = xcd_tile(blockIdx.x, gridDim.x);
+    // One block fits a CU, two with one component in FP32 arithmetic (77 KB of
+    // LDS): a round is 256 or 512 blocks.  Runs per round instead of one run of
+    // the whole grid: 181^3 in FP64, 690 blocks, 948 us against 1050.
+    const int L = xcd_tile(blockIdx.x, gridDim.x, NC == 1 && sizeof(typename ST::T) == 4 ? 512 : 256);
     if constexpr (kPair<ST, NC, FS>) {
         using W = typename PairWordOf<ST>::W;
         __shared__ PairShared<ST, CNS> sh;
         step_tile_pair<ST, CNS, FS, ONE, RND, AUX>(a, reinterpret_cast<const W*>(A), reinterpret_cast<W*>(B), ns, L,
                                                       a.t, sh);
     } else {
-        __shared__ TileShared<ST, NC, CNS, TX, TY> sh;
-        step_tile<ST, NC, CNS, TX, TY, FS, ONE>(a, A, B, ns, L, a.t, sh);
+        __shared__ TileShared<ST, NC, CNS> sh;
+        step_tile<ST, NC, CNS, FS, ONE, AUX>(a, A, B, ns, L, a.t, sh);
     }
 }
 
@@ -837,8 +785,8 @@ struct BatchHeader {
 
 constexpr size_t kBatchEntryOffset = 64;
 
-template <typename ST, int NC, int CNS, int TX, int TY, int AUX>
-__global__ __launch_bounds__((kThreads<ST, NC, TX, TY>)) void k_step_batch(const char* __restrict__ table, int k)
+template <typename ST, int NC, int CNS, int AUX>
+__global__ __launch_bounds__((kThreads<ST, NC>)) void k_step_batch(const char* __restrict__ table, int k)
 {
     using T = typename ST::T;
     using E = typename ST::E;
@@ -851,7 +799,7 @@ __global__ __launch_bounds__((kThreads<ST, NC, TX, TY>)) void k_step_batch(const
     // (neighbouring tiles re-read each other's edge cells through its L2)
     const int nb = gridDim.x;
     const int b0 = (nb & 7) == 0 ? (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
-    using Shared = std::conditional_t<kPair<ST, NC>, PairShared<ST, CNS>, TileShared<ST, NC, CNS, TX, TY>>;
+    using Shared = std::conditional_t<kPair<ST, NC>, PairShared<ST, CNS>, TileShared<ST, NC, CNS>>;
     __shared__ Shared sh;
     for (int w = b0; w < total; w += nb) {
         int lo = 0, hi = nd - 1;  // last domain with tile_begin <= w
@@ -878,9 +826,9 @@ __global__ __launch_bounds__((kThreads<ST, NC, TX, TY>)) void k_step_batch(const
                 step_tile_pair<ST, CNS, kForcingShanChen, false, kRoundNearest, AUX>(e.a, src, dst, e.ns,
                                                                                      w - e.tile_begin, tk, sh);
         } else
-            step_tile<ST, NC, CNS, TX, TY, kForcingShanChen>(e.a, static_cast<const E*>(e.buf[cur]),
-                                                             static_cast<E*>(const_cast<void*>(e.buf[1 - cur])), e.ns,
-                                                             w - e.tile_begin, e.a.t + static_cast<uint32_t>(k), sh);
+            step_tile<ST, NC, CNS, kForcingShanChen, false, AUX>(
+                e.a, static_cast<const E*>(e.buf[cur]), static_cast<E*>(const_cast<void*>(e.buf[1 - cur])), e.ns,
+                w - e.tile_begin, e.a.t + static_cast<uint32_t>(k), sh);
     }
 }
 
@@ -1335,11 +1283,18 @@ bool pair_layout(int storage, int ncomp, int forcing)
 }
 
 
-bool tile_supported(int storage, int ncomp, int tx, int ty, int forcing)
+void tile_limits(const Problem& p, int* cells, int* rows)
 {
-    if (pair_layout(storage, ncomp, forcing))
-        return tx >= 1 && ty >= 1 && tx <= kPairW && ty <= kPairH && tx * ty <= kPairCells;
-    return (tx == 128 && ty == 4) || (tx == 64 && (ty == 4 || ty == 8)) || (tx == 32 && (ty == 4 || ty == 8 || ty == 16));
+    const bool pair = pair_layout(p.storage, p.ncomp, p.forcing);
+    *cells = pair ? kPairCells : split_cells(p.storage == kF64, p.ncomp);
+    *rows = pair ? kPairH : split_rows(p.storage == kF64, p.ncomp, p.c_ns);
+}
+
+bool tile_supported(const Problem& p, int tx, int ty)
+{
+    int cells, rows;
+    tile_limits(p, &cells, &rows);
+    return tx >= 1 && ty >= 1 && tx <= 64 && ty <= rows && tx * ty <= cells;
 }
 
 int storage_bytes(int storage)
@@ -1353,7 +1308,7 @@ int storage_bytes(int storage)
     }
 }
 
-template <typename ST, int NC, int CNS, int TX, int TY, int FS, bool ONE>
+template <typename ST, int NC, int CNS, int FS, bool ONE>
 static hipError_t step_t(const Problem& p, const Launch& l, int64_t t, const void* A, void* B, const float* ns,
                          hipStream_t st)
 {
@@ -1368,78 +1323,48 @@ static hipError_t step_t(const Problem& p, const Launch& l, int64_t t, const voi
     a.nzc = (p.nz + l.zchunk - 1) / l.zchunk;
     a.t = static_cast<uint32_t>(t);
     const int nblocks = a.ntx * a.nty * a.nzc;
-    // the pair kernel is compiled per rounding mode; the split kernels
+    // one instance per store policy (FP64 and one plane keep non-temporal
+    // stores), and of the pair kernel per rounding mode; the split kernels
     // branch on it (their two store sequences are alike)
-    // and per store policy
     auto go = [&](auto rnd, auto aux) {
-        hipLaunchKernelGGL((k_step<ST, NC, CNS, TX, TY, FS, ONE, decltype(rnd)::value, decltype(aux)::value>),
-                           dim3(nblocks), dim3(kThreads<ST, NC, TX, TY, FS>), 0, st, a, static_cast<const E*>(A),
-                           static_cast<E*>(B), ns);
+        hipLaunchKernelGGL((k_step<ST, NC, CNS, FS, ONE, decltype(rnd)::value, decltype(aux)::value>), dim3(nblocks),
+                           dim3(kThreads<ST, NC, FS>), 0, st, a, static_cast<const E*>(A), static_cast<E*>(B), ns);
     };
     using Nt = std::integral_constant<int, kNT>;
+    using Cached = std::integral_constant<int, ONE || sizeof(E) == 8 ? kNT : 0>;
+    auto policy = [&](auto rnd) { l.nt_stores ? go(rnd, Nt{}) : go(rnd, Cached{}); };
     if constexpr (kPair<ST, NC, FS>) {
-        // FP32 rounds to nearest; one plane (and the GS-WBS) keep one policy
-        using Sr = std::integral_constant<int, sizeof(E) == 2 ? kRoundStochastic : kRoundNearest>;
-        using Near = std::integral_constant<int, kRoundNearest>;
-        constexpr bool BOTH = !ONE && FS == kForcingShanChen;
-        using Cached = std::integral_constant<int, BOTH ? 0 : kNT>;
-        const bool cached = BOTH && !l.nt_stores;
-        if (p.stochastic) cached ? go(Sr{}, Cached{}) : go(Sr{}, Nt{});
-        else cached ? go(Near{}, Cached{}) : go(Near{}, Nt{});
+        // FP32 rounds to nearest
+        if (sizeof(E) == 2 && p.stochastic)
+            policy(std::integral_constant<int, sizeof(E) == 2 ? kRoundStochastic : kRoundNearest>{});
+        else policy(std::integral_constant<int, kRoundNearest>{});
     } else {
-        go(std::integral_constant<int, kRoundEither>{}, Nt{});
+        policy(std::integral_constant<int, kRoundEither>{});
     }
     return hipGetLastError();
 }
 
-// One forcing scheme, with its one-plane instance.
-template <typename ST, int NC, int CNS, int TX, int TY, int FS>
+template <typename ST, int NC, int CNS>
 static hipError_t step_fs(const Problem& p, const Launch& l, int64_t t, const void* A, void* B, const float* ns,
                           hipStream_t st)
 {
-    return p.nz == 1 ? step_t<ST, NC, CNS, TX, TY, FS, true>(p, l, t, A, B, ns, st)
-                     : step_t<ST, NC, CNS, TX, TY, FS, false>(p, l, t, A, B, ns, st);
-}
-
-// Tile shapes (TX x TY cells per block) compiled in.
-template <typename ST, int NC, int CNS>
-static hipError_t step_ty(const Problem& p, const Launch& l, int64_t t, const void* A, void* B, const float* ns,
-                          hipStream_t st)
-{
     constexpr int SC = kForcingShanChen, GUO = kForcingGuo;
-    if (!tile_supported(p.storage, NC, l.tile_x, l.tile_y, p.forcing)) return hipErrorInvalidValue;
-    const bool t8 = l.tile_x == 64 && l.tile_y == 8, t4 = l.tile_x == 64 && l.tile_y == 4;
-    if (p.forcing == GUO) {
-        if constexpr (kPair<ST, NC, GUO>) {
-            return step_fs<ST, NC, CNS, 64, 8, GUO>(p, l, t, A, B, ns, st);
-        } else {
-            if (t8) return step_fs<ST, NC, CNS, 64, 8, GUO>(p, l, t, A, B, ns, st);
-            if (t4) return step_fs<ST, NC, CNS, 64, 4, GUO>(p, l, t, A, B, ns, st);
-            return hipErrorInvalidValue;  // default tiles only
-        }
-    }
-    if constexpr (kPair<ST, NC>) {
-        // one instance takes every tile (the 64, 8 only name it)
-        return step_fs<ST, NC, CNS, 64, 8, SC>(p, l, t, A, B, ns, st);
-    } else {
-        if (t8) return step_fs<ST, NC, CNS, 64, 8, SC>(p, l, t, A, B, ns, st);
-        if (t4) return step_fs<ST, NC, CNS, 64, 4, SC>(p, l, t, A, B, ns, st);
-        if (p.nz == 1) return hipErrorInvalidValue;  // default tiles only
-        if (l.tile_x == 128 && l.tile_y == 4) return step_t<ST, NC, CNS, 128, 4, SC, false>(p, l, t, A, B, ns, st);
-        if (l.tile_x == 32 && l.tile_y == 4) return step_t<ST, NC, CNS, 32, 4, SC, false>(p, l, t, A, B, ns, st);
-        if (l.tile_x == 32 && l.tile_y == 8) return step_t<ST, NC, CNS, 32, 8, SC, false>(p, l, t, A, B, ns, st);
-        if (l.tile_x == 32 && l.tile_y == 16) return step_t<ST, NC, CNS, 32, 16, SC, false>(p, l, t, A, B, ns, st);
-        return hipErrorInvalidValue;
-    }
+    if (!tile_supported(p, l.tile_x, l.tile_y)) return hipErrorInvalidValue;
+    const bool one = p.nz == 1;
+    if (p.forcing == GUO)
+        return one ? step_t<ST, NC, CNS, GUO, true>(p, l, t, A, B, ns, st)
+                   : step_t<ST, NC, CNS, GUO, false>(p, l, t, A, B, ns, st);
+    return one ? step_t<ST, NC, CNS, SC, true>(p, l, t, A, B, ns, st)
+               : step_t<ST, NC, CNS, SC, false>(p, l, t, A, B, ns, st);
 }
 
 template <typename ST>
 static hipError_t step_st(const Problem& p, const Launch& l, int64_t t, const void* A, void* B, const float* ns,
                           hipStream_t st)
 {
-    if (p.ncomp == 1) return step_ty<ST, 1, 1>(p, l, t, A, B, ns, st);
-    if (p.c_ns == 1) return step_ty<ST, 2, 1>(p, l, t, A, B, ns, st);
-    return step_ty<ST, 2, 2>(p, l, t, A, B, ns, st);
+    if (p.ncomp == 1) return step_fs<ST, 1, 1>(p, l, t, A, B, ns, st);
+    if (p.c_ns == 1) return step_fs<ST, 2, 1>(p, l, t, A, B, ns, st);
+    return step_fs<ST, 2, 2>(p, l, t, A, B, ns, st);
 }
 
 hipError_t launch_step(const Problem& p, const Launch& l, int64_t t, const void* A, void* B, const float* ns,
@@ -1776,55 +1701,42 @@ int batch_encode(int storage, const BatchDomain* d, int n, void* host)
     return storage == kF64 ? batch_encode_t<double>(d, n, host) : batch_encode_t<float>(d, n, host);
 }
 
-// Kernel of a store policy (the split layout has one).
-template <typename ST, int NC, int CNS, int TX, int TY>
+// Kernel of a store policy (FP64 has one).
+template <typename ST, int NC, int CNS>
 static auto batch_kernel(bool nt)
 {
-    constexpr int CACHED = kPair<ST, NC> ? 0 : kNT;
-    return nt ? k_step_batch<ST, NC, CNS, TX, TY, kNT> : k_step_batch<ST, NC, CNS, TX, TY, CACHED>;
+    constexpr int CACHED = sizeof(typename ST::E) == 8 ? kNT : 0;
+    return nt ? k_step_batch<ST, NC, CNS, kNT> : k_step_batch<ST, NC, CNS, CACHED>;
 }
 
-template <typename ST, int NC, int CNS, int TX, int TY>
+template <typename ST, int NC, int CNS>
 static hipError_t batch_t(const void* table, int k, int grid, bool nt, hipStream_t st)
 {
-    hipLaunchKernelGGL((batch_kernel<ST, NC, CNS, TX, TY>(nt)), dim3(grid), dim3(kThreads<ST, NC, TX, TY>), 0, st,
+    hipLaunchKernelGGL((batch_kernel<ST, NC, CNS>(nt)), dim3(grid), dim3(kThreads<ST, NC>), 0, st,
                        static_cast<const char*>(table), k);
     return hipGetLastError();
 }
 
-template <typename ST, int NC, int CNS, int TX, int TY>
+template <typename ST, int NC, int CNS>
 static int batch_occ_t()
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<ST, NC, CNS, TX, TY>(true),
-                                                     kThreads<ST, NC, TX, TY>, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<ST, NC, CNS>(true), kThreads<ST, NC>, 0) !=
+        hipSuccess)
         return 1;
     return n > 0 ? n : 1;
 }
 
-// One function for every (format, components, n_s fields, tile) of the
-// batched kernel: f receives the compiled instance's launcher and occupancy.
-template <typename ST, int NC, int CNS, typename F>
-static hipError_t batch_tile(int tx, int ty, F&& f)
-{
-    if constexpr (kPair<ST, NC>) {
-        // one instance takes every tile (the 64, 8 only name it)
-        return f(batch_t<ST, NC, CNS, 64, 8>, batch_occ_t<ST, NC, CNS, 64, 8>);
-    } else {
-        if (tx == 64 && ty == 8) return f(batch_t<ST, NC, CNS, 64, 8>, batch_occ_t<ST, NC, CNS, 64, 8>);
-        if (tx == 32 && ty == 8) return f(batch_t<ST, NC, CNS, 32, 8>, batch_occ_t<ST, NC, CNS, 32, 8>);
-        return hipErrorInvalidValue;
-    }
-}
-
+// One function for every (format, components, n_s fields) of the batched
+// kernel: f receives the compiled instance's launcher and occupancy.
 template <typename F>
-static hipError_t batch_dispatch(int storage, int ncomp, int c_ns, int tx, int ty, F&& f)
+static hipError_t batch_dispatch(int storage, int ncomp, int c_ns, F&& f)
 {
     return by_storage(storage, [&](auto tag) {
         using ST = decltype(tag);
-        if (ncomp == 1) return batch_tile<ST, 1, 1>(tx, ty, f);
-        if (c_ns == 1) return batch_tile<ST, 2, 1>(tx, ty, f);
-        return batch_tile<ST, 2, 2>(tx, ty, f);
+        if (ncomp == 1) return f(batch_t<ST, 1, 1>, batch_occ_t<ST, 1, 1>);
+        if (c_ns == 1) return f(batch_t<ST, 2, 1>, batch_occ_t<ST, 2, 1>);
+        return f(batch_t<ST, 2, 2>, batch_occ_t<ST, 2, 2>);
     });
 }
 
@@ -1834,21 +1746,20 @@ bool batch_tile_supported(int storage, int ncomp, int tx, int ty)
     return (tx == 64 && ty == 8) || (tx == 32 && ty == 8);
 }
 
-int batch_blocks_per_cu(int storage, int ncomp, int c_ns, int tile_x, int tile_y)
+int batch_blocks_per_cu(int storage, int ncomp, int c_ns)
 {
     int n = 1;
-    (void)batch_dispatch(storage, ncomp, c_ns, tile_x, tile_y, [&](auto, auto occ) {
+    (void)batch_dispatch(storage, ncomp, c_ns, [&](auto, auto occ) {
         n = occ();
         return hipSuccess;
     });
     return n;
 }
 
-hipError_t launch_step_batch(int storage, int ncomp, int c_ns, int tile_x, int tile_y, const void* table, int k,
-                             int grid, bool nt, hipStream_t st)
+hipError_t launch_step_batch(int storage, int ncomp, int c_ns, const void* table, int k, int grid, bool nt,
+                             hipStream_t st)
 {
-    return batch_dispatch(storage, ncomp, c_ns, tile_x, tile_y,
-                          [&](auto launch, auto) { return launch(table, k, grid, nt, st); });
+    return batch_dispatch(storage, ncomp, c_ns, [&](auto launch, auto) { return launch(table, k, grid, nt, st); });
 }
 
 }  // namespace hm

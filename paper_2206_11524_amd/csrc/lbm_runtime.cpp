@@ -107,23 +107,19 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
                !hm::choose_box(p, cus, &l.bx, &l.by, &l.bz)) {
         l.bx = 0;
     }
-    // FP64 with two components needs the smaller tile to stay within the
-    // register file (no spills)
-    const bool wide = p.storage == hm::kF64 && p.ncomp == 2;
     const bool pair = hm::pair_layout(p.storage, p.ncomp, p.forcing);
-    const int dflt_y = (p.ny >= 8 && !wide) ? 8 : 4;
+    int cells, rows;
+    hm::tile_limits(p, &cells, &rows);
     const int env_x = env_int("LBM_TILE_X", 0), env_y = env_int("LBM_TILE_Y", 0), env_z = env_int("LBM_ZCHUNK", 0);
     l.tile_x = env_x ? env_x : 64;
-    l.tile_y = env_y ? env_y : dflt_y;
-    const bool given = hm::tile_supported(p.storage, p.ncomp, l.tile_x, l.tile_y, p.forcing) &&
-                       (pair || !(p.forcing == hm::kForcingGuo || p.nz == 1) ||
-                        (l.tile_x == 64 && (l.tile_y == 8 || l.tile_y == 4)));
-    if (!given) {  // the split GS-WBS and one-plane domains use the default widths only
+    l.tile_y = env_y ? env_y : std::min(cells / 64, p.ny);
+    const bool given = (env_x || env_y) && hm::tile_supported(p, l.tile_x, l.tile_y);
+    if (!given) {
         l.tile_x = 64;
-        l.tile_y = dflt_y;
+        l.tile_y = cells / 64;
     }
     const int64_t ncu = std::max(cus, 1);
-    const int64_t word = 2 * hm::storage_bytes(p.storage);
+    const int64_t word = hm::storage_bytes(p.storage) * (pair ? 2 : 1);
     auto part = [](int n, int k) { return (n + k - 1) / k; };
     // One block fits a CU (registers and LDS), so blocks run in rounds of one
     // per CU, and a block takes about (chunk + 8) plane times: the halo planes,
@@ -135,32 +131,44 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     // tiles per CU: a small domain would leave most CUs idle, and its halo
     // re-reads are L2 hits.
     //
-    // The pair sweep takes any tile of up to 512 cells.  Its plane time falls
-    // by 30 % at most with the lanes that have a cell, rises with shorter rows
-    // (8 / w), and in domains many times the caches' size by 8 % for rows that
-    // split cache lines or fewer than eight of 64 (fitted to 20 domains in FP16
-    // and FP32, some 26 tiles and chunks each: 1 % off the best on average).
+    // The sweeps take any tile within tile_limits.  A plane time falls by 30 % at
+    // most with the lanes that have a cell, rises with shorter rows (8 / w), and in
+    // domains many times the caches' size by 8 % for rows that split cache lines
+    // or fewer than eight of 64 (elsewhere those lose ties only; fitted to 20
+    // domains in FP16 and FP32, some 26 tiles and chunks each: 1 % off the best on
+    // average).
     // Even parts of the domain are tried beside 64 x 8: 131^3 in FP16 takes 44 x 11
     // tiles (108 us a step, 136 with 64 x 8), 100^3 50 x 9 (48 / 65), 72^3 in FP32
     // 36 x 11 (29 / 42); 192^3 and 224^3 keep 64 x 8 (271 against 277 us with 64 x 7,
-    // 429 against 516 with 56 x 9 in FP16).
+    // 429 against 516 with 56 x 9 in FP16); one component 150^3 50 x 10 (FP32 115 /
+    // 167, FP16 76 / 104); the GS-WBS in FP32 150 x 150 x 100 50 x 10 (203 / 258).
     //
     // In a batched launch every block strides over many tiles: there the tile of
     // the least columns x plane time is taken, with 60 % of the time following
     // the lanes in FP32, where enough tiles fill the memory (eight 96^3 domains:
     // 501 us a step with 64 x 8 tiles, 523 with 48 x 10; twelve 67^3 431 and 312
     // with 34 x 14; in FP16 317 and 299, 276 and 188).
+    //
+    // Two components in FP64 are nearer the memory's rate: 60 % of the plane time
+    // follows the lanes, and split lines cost 12 % from a quarter of that size on
+    // (200 x 200 x 100: 64 x 4 tiles in one round of 200 blocks 638 us, 50 x 5 in two
+    // rounds 715; 131^3: 44 x 5 363, 64 x 4 416).
+    const bool wide = p.storage == hm::kF64 && p.ncomp == 2;
+    const double follow = wide ? 0.6 : 0.3;
+    const bool large = p.N > (wide ? 1500000 : 6000000);
     double best = -1.0, batch_best = -1.0;
     l.batch_x = 64;
-    l.batch_y = 8;
+    l.batch_y = cells / 64;
     auto consider = [&](int w, int h) {
         const int64_t cols = static_cast<int64_t>((p.nx + w - 1) / w) * ((p.ny + h - 1) / h);
-        const double lanes = static_cast<double>(p.nx) * p.ny / (static_cast<double>(cols) * (pair ? 512 : w * h));
-        const double lines = h * w == 512 && w % 32 == 0 ? 1.0 : 1.08;
-        const double plane = pair ? (0.7 + 0.3 * lanes) * (1.0 + 8.0 / w) * (p.N > 6000000 ? lines : 1.0) : 1.0;
-        const double share = p.storage == hm::kF32 ? 0.6 : 0.3;
-        const double column = static_cast<double>(cols) * (1.0 - share + share * lanes) * (1.0 + 8.0 / w) * lines;
-        if (pair && (batch_best < 0.0 || column < batch_best)) {
+        const double lanes = static_cast<double>(p.nx) * p.ny / (static_cast<double>(cols) * cells);
+        const double lines = h * w == cells && w % 32 == 0 ? 1.0 : (wide ? 1.12 : 1.08);
+        const double tie = lines > 1.0 ? 1.005 : 1.0;
+        const double plane = (1.0 - follow + follow * lanes) * (1.0 + 8.0 / w) * (large ? lines : tie);
+        const double share = p.storage == hm::kF32 || p.storage == hm::kF64 ? 0.6 : 0.3;
+        const double column =
+            static_cast<double>(cols) * (1.0 - share + share * lanes) * (1.0 + 8.0 / w) * lines;
+        if (batch_best < 0.0 || column < batch_best) {
             batch_best = column;
             l.batch_x = w;
             l.batch_y = h;
@@ -183,27 +191,28 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
             if (z < min_chunk) break;
         }
     };
-    if (pair && !env_x && !env_y && p.nz > 1) {
+    if (!given && p.nz > 1) {
         const int k0 = part(p.nx, 64);
         for (int k = k0 - 1; k <= k0 + 3; ++k) {
             const int w = k < k0 ? 64 : part(p.nx, k);
             if (w > p.nx || (k > k0 && w < 24)) continue;
-            int h = part(p.ny, part(p.ny, std::min(std::min(16, 512 / w), p.ny)));
+            int h = part(p.ny, part(p.ny, std::min(std::min(rows, cells / w), p.ny)));
             for (;;) {
                 consider(w, h);
-                if (h == 1 || h * w < 256) break;
+                if (h == 1 || h * w < cells / 2) break;
                 h = part(p.ny, part(p.ny, h - 1));
             }
         }
     }
-    if (best < 0.0) consider(l.tile_x, l.tile_y);  // one tile in the split layout, or as given
+    if (best < 0.0) consider(l.tile_x, l.tile_y);  // as given, or one plane
     // Non-temporal stores keep the written state out of the caches' way, but
     // where a tile's rows start or end inside a 128-byte line the two tiles that
     // share it each write part of it, and only a cached line is merged before it
     // goes out: 131^3 in FP32 169 us a step with cached stores against 205, 100^3 in
     // FP16 48 against 56; with whole lines non-temporal stores are the faster ones
     // (256^3 in FP32 970 against 997).
-    l.nt_stores = l.tile_x * word % 128 == 0 && p.nx * word % 128 == 0;
+    // FP64 keeps them (150^3 548 against 577, 160^3 528 against 550).
+    l.nt_stores = p.storage == hm::kF64 || (l.tile_x * word % 128 == 0 && p.nx * word % 128 == 0);
     return l;
 }
 
