@@ -225,7 +225,9 @@ using namespace hm_rt;
         if ((expr) != hipSuccess) return LBM_EDEVICE;  \
     } while (0)
 
-int hm_rt::compute_totals(lbm_ctx* c, bool fields, bool forces, lbm_totals* tot)
+// Queue the FP64 diagnostics (the per-cell fields and the totals in scratch); a
+// caller that only launches on from the fields need not wait for the totals.
+static int launch_fields(lbm_ctx* c, bool fields, bool forces)
 {
     double* rho = reinterpret_cast<double*>(c->scratch + c->sl.rho);
     double* u = reinterpret_cast<double*>(c->scratch + c->sl.u);
@@ -234,6 +236,14 @@ int hm_rt::compute_totals(lbm_ctx* c, bool fields, bool forces, lbm_totals* tot)
     double* tots = reinterpret_cast<double*>(c->scratch + c->sl.totals);
     HIP_TRY(hm::launch_diagnostics(c->prob, c->buf[c->cur], c->ns, forces || fields, rho, fields ? u : nullptr,
                                    fields ? p : nullptr, part, tots, c->stream));
+    return LBM_OK;
+}
+
+int hm_rt::compute_totals(lbm_ctx* c, bool fields, bool forces, lbm_totals* tot)
+{
+    const int rc = launch_fields(c, fields, forces);
+    if (rc) return rc;
+    const double* tots = reinterpret_cast<const double*>(c->scratch + c->sl.totals);
     double h[5];
     HIP_TRY(hipMemcpyAsync(h, tots, sizeof(h), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
@@ -517,7 +527,7 @@ int lbm_fill_state_get(lbm_ctx* c, const lbm_fill_query* q, lbm_fill_state* out)
     if (!slab_ok(q->inlet_lo, q->inlet_hi, true) || !slab_ok(q->outlet_lo, q->outlet_hi, true) ||
         !slab_ok(q->pore_lo, q->pore_hi, false) || !std::isfinite(q->threshold))
         return LBM_EINVAL;
-    const int rc = compute_totals(c, true, true, nullptr);  // FP64 densities and pressure into the scratch
+    const int rc = launch_fields(c, true, true);  // FP64 densities and pressure into the scratch
     if (rc) return rc;
     hm::FillQuery f{q->axis, q->inlet_lo, q->inlet_hi, q->outlet_lo, q->outlet_hi, q->pore_lo, q->pore_hi, q->comp,
                     q->threshold};
@@ -542,7 +552,7 @@ int lbm_permeability_get(lbm_ctx* c, int32_t axis, lbm_permeability* out)
     if (!c || !out || axis < 0 || axis > 2) return LBM_EINVAL;
     const double F = c->prm.F_ext[axis];
     if (F == 0.0 || (c->prm.ncomp == 2 && c->prm.tau[0] != c->prm.tau[1])) return LBM_EINVAL;
-    const int rc = compute_totals(c, true, true, nullptr);  // FP64 densities and u_macro into the scratch
+    const int rc = launch_fields(c, true, true);  // FP64 densities and u_macro into the scratch
     if (rc) return rc;
     double* part = reinterpret_cast<double*>(c->scratch + c->sl.partials);
     double* tots = reinterpret_cast<double*>(c->scratch + c->sl.totals);
