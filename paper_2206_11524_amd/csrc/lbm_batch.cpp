@@ -107,8 +107,9 @@ class BatchRunner {
         (void)hipGetLastError();
     }
 
-    // Whole 128-byte lines in every row of the domain's tiles: non-temporal
-    // stores; otherwise the rows' shared lines are merged in the caches.
+    // Whole 128-byte lines in every row of the domain's tiles.  A launch has one
+    // store policy: non-temporal where most of its cells are in such domains,
+    // otherwise cached, which merges the lines that tiles share.
     static bool whole_lines(const hm::BatchDomain& d)
     {
         if (d.prob.storage == hm::kF64) return true;  // one policy
@@ -130,17 +131,18 @@ class BatchRunner {
         // re-reads cost little there)
         balanced_.assign(d, d + n);
         int64_t cols = 0, tiles16 = 0;
-        bool nt = true;
+        int64_t whole = 0;  // cells in whole lines, less the others
         for (hm::BatchDomain& b : balanced_) {
             if (!own_tiles_ && hm::tile_supported(b.prob, tx_, ty_)) {
                 b.tile_x = tx_;
                 b.tile_y = ty_;
             }
-            nt = nt && whole_lines(b);
+            whole += whole_lines(b) ? b.prob.N : -b.prob.N;
             const int64_t c = columns(b);
             cols += c;
             tiles16 += c * ((b.prob.nz + 15) / 16);
         }
+        const bool nt = whole >= 0;
         const int64_t min_chunk = tiles16 >= 2 * static_cast<int64_t>(cus_) ? 16 : 4;
         auto chunk_of = [&](const hm::BatchDomain& b, int64_t per_cols) {
             const int64_t chunks = std::max<int64_t>(per_cols, (b.prob.nz + maxc_ - 1) / maxc_);
@@ -358,8 +360,9 @@ int lbm_group_create(lbm_ctx* const* ctxs, int32_t n, lbm_group** out)
     g->ctx.assign(ctxs, ctxs + n);
     const lbm_params& p = ctxs[0]->prm;
     const int tx = hm_rt::env_int("LBM_BATCH_TILE_X", 0), ty = hm_rt::env_int("LBM_BATCH_TILE_Y", 0);
-    bool nt = true;
-    for (const lbm_ctx* c : g->ctx) nt = nt && BatchRunner::whole_lines(domain_of(c, 0));
+    int64_t whole = 0;
+    for (const lbm_ctx* c : g->ctx) whole += BatchRunner::whole_lines(domain_of(c, 0)) ? c->prob.N : -c->prob.N;
+    const bool nt = whole >= 0;
     const int rc = g->runner.init(p.storage, p.ncomp, p.c_ns, tx, ty, n, hm_rt::env_int("LBM_GRAPH_STEPS", 16), nt,
                                   ctxs[0]->stream);
     if (rc) {

@@ -145,9 +145,13 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     //
     // In a batched launch every block strides over many tiles: there the tile of
     // the least columns x plane time is taken, with 60 % of the time following
-    // the lanes in FP32, where enough tiles fill the memory (eight 96^3 domains:
-    // 501 us a step with 64 x 8 tiles, 523 with 48 x 10; twelve 67^3 431 and 312
-    // with 34 x 14; in FP16 317 and 299, 276 and 188).
+    // the lanes in FP32, where enough tiles fill the memory, and a higher price of
+    // short rows (eight 96^3 domains in FP32: 501 us a step with 64 x 8 tiles, 486
+    // with 48 x 10, 518 with 32 x 16; twelve 67^3 431 and 310 with 34 x 14; in FP16 276
+    // and 188), and no tile that splits the lines of rows
+    // that are whole ones (64 domains of edges 32 to 128, all but 48 whole lines,
+    // in FP16: 38.9 million cells at 25.3 GLUPS with such tiles and cached stores,
+    // 26.8 with whole lines and non-temporal stores).
     //
     // Two components in FP64 are nearer the memory's rate: 60 % of the plane time
     // follows the lanes, and split lines cost 12 % from a quarter of that size on
@@ -166,9 +170,12 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
         const double tie = lines > 1.0 ? 1.005 : 1.0;
         const double plane = (1.0 - follow + follow * lanes) * (1.0 + 8.0 / w) * (large ? lines : tie);
         const double share = p.storage == hm::kF32 || p.storage == hm::kF64 ? 0.6 : 0.3;
+        const bool aligned = p.nx * word % 128 == 0 && w * word % 128 == 0;
+        const double narrow = 1.0 + (hm::storage_bytes(p.storage) == 2 ? 20.0 : 16.0) / w;
         const double column =
-            static_cast<double>(cols) * (1.0 - share + share * lanes) * (1.0 + 8.0 / w) * lines;
-        if (batch_best < 0.0 || column < batch_best) {
+            static_cast<double>(cols) * (1.0 - share + share * lanes) * narrow * (aligned ? 1.0 : 1.08);
+        const bool splits = p.nx * word % 128 == 0 && w * word % 128 != 0;
+        if (!splits && (batch_best < 0.0 || column < batch_best)) {
             batch_best = column;
             l.batch_x = w;
             l.batch_y = h;
