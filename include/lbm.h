@@ -69,8 +69,8 @@ typedef enum {
  * equilibrium velocity of Eq. (SC_u_eq).  LBM_FORCING_GUO is the grayscale
  * scheme the paper contrasts it with (appendix on Guo vs. Shan-Chen forcing,
  * Eq. GS-WBS): equilibrium at u_macro of Eq. (HMCSC_u_macro) plus (1 - n_s)
- * times the forcing term of Guo, Zheng and Shi (2002).  The GS-WBS runs with
- * the default tile shapes and is not accepted by the batched server. */
+ * times the forcing term of Guo, Zheng and Shi (2002).  The GS-WBS is not
+ * accepted by the batched server. */
 typedef enum {
     LBM_FORCING_SHAN_CHEN = 0,
     LBM_FORCING_GUO = 1

@@ -492,16 +492,6 @@ __device__ __forceinline__ void pull_raw(const rsrc_t r3[3], uint32_t dir_bytes,
         e[i] = ST::bld(r3[CZ[i] + 1], q.o[CY[i] + 1][CX[i] + 1], static_cast<uint32_t>(i) * dir_bytes);
 }
 
-template <typename ST, typename T>
-__device__ __forceinline__ void pull(const rsrc_t r3[3], uint32_t dir_bytes, const PlaneOffs& q, T inv_scale,
-                                     T h[kQ])
-{
-#pragma unroll
-    for (int i = 0; i < kQ; ++i)
-        h[i] = ST::dec(ST::bld(r3[CZ[i] + 1], q.o[CY[i] + 1][CX[i] + 1], static_cast<uint32_t>(i) * dir_bytes),
-                       inv_scale);
-}
-
 template <typename T>
 __device__ __forceinline__ T sum19(const T h[kQ])
 {
