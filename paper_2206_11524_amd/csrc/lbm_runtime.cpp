@@ -131,12 +131,21 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     // tiles per CU: a small domain would leave most CUs idle, and its halo
     // re-reads are L2 hits.
     //
-    // The sweeps take any tile within tile_limits.  A plane time falls by 30 % at
-    // most with the lanes that have a cell, rises with shorter rows (8 / w), and in
-    // domains many times the caches' size by 8 % for rows that split cache lines
-    // or fewer than eight of 64 (elsewhere those lose ties only; fitted to 20
-    // domains in FP16 and FP32, some 26 tiles and chunks each: 1 % off the best on
-    // average).
+    // The sweeps take any tile within tile_limits.  A plane time falls with the
+    // lanes that have a cell, by 30 % at most where the domain streams from
+    // memory and by 15 % where the caches hold both buffers (the planes then wait
+    // on latency: 64 x 64 x 129 with 6 of 8 rows and 6 planes per block takes 45 us in
+    // FP32 and 33 in FP16, whole 64 x 8 tiles of 5 planes 41 and 29; 63^3 in FP64
+    // with 63 x 2 and 8 planes 54, with 63 x 4 and 4 planes 38).  It rises with
+    // shorter rows (8 / w) and with tiles that split cache lines: by 30 % beyond the
+    // caches where the rows of the domain are whole ones (160 x 242 x 96 with one
+    // component in FP32, 54-wide tiles 172 us, 32-wide 108), otherwise by 3 % in
+    // FP64 and by 8 % in domains many times the caches' size (12 % with two
+    // components in FP64).  Lines count 64 bytes in FP64, whose stores are always
+    // non-temporal and write such sectors (200 x 200 x 100 with one component: 50-wide
+    // tiles 319 us, 40-wide 247), 128 where cached stores merge them.  Over 324
+    // domains of 1.4 thousand to 14 million cells in six formats, up to 16 tiles and
+    // chunks each, the choice is 1.2 % off the best on average.
     // Even parts of the domain are tried beside 64 x 8: 131^3 in FP16 takes 44 x 11
     // tiles (108 us a step, 136 with 64 x 8), 100^3 50 x 9 (48 / 65), 72^3 in FP32
     // 36 x 11 (29 / 42); 192^3 and 224^3 keep 64 x 8 (271 against 277 us with 64 x 7,
@@ -153,22 +162,23 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     // in FP16: 38.9 million cells at 25.3 GLUPS with such tiles and cached stores,
     // 26.8 with whole lines and non-temporal stores).
     //
-    // Two components in FP64 are nearer the memory's rate: 60 % of the plane time
-    // follows the lanes, and split lines cost 12 % from a quarter of that size on
-    // (200 x 200 x 100: 64 x 4 tiles in one round of 200 blocks 638 us, 50 x 5 in two
-    // rounds 715; 131^3: 44 x 5 363, 64 x 4 416).
-    const bool wide = p.storage == hm::kF64 && p.ncomp == 2;
-    const double follow = wide ? 0.6 : 0.3;
-    const bool large = p.N > (wide ? 1500000 : 6000000);
+    // Two components in FP64 take 256 cells: 200 x 200 x 100 64 x 4 tiles 600 us, 50 x 5
+    // 638; 131^3 44 x 5 363, 64 x 4 407.
+    const int64_t state = p.N * hm::kQ * hm::storage_bytes(p.storage) * p.ncomp;
+    const bool f64 = p.storage == hm::kF64;
+    const bool cached = state < (int64_t(1) << 27);  // both buffers within the 256 MB of the last cache
+    const double follow = cached ? 0.15 : 0.3;
+    const double split = f64 ? (p.ncomp == 2 && p.N > 1500000 ? 1.12 : 1.03) : (p.N > 6000000 ? 1.08 : 1.005);
+    const int64_t line = f64 ? 64 : 128;
     double best = -1.0, batch_best = -1.0;
     l.batch_x = 64;
     l.batch_y = cells / 64;
     auto consider = [&](int w, int h) {
         const int64_t cols = static_cast<int64_t>((p.nx + w - 1) / w) * ((p.ny + h - 1) / h);
         const double lanes = static_cast<double>(p.nx) * p.ny / (static_cast<double>(cols) * cells);
-        const double lines = h * w == cells && w % 32 == 0 ? 1.0 : (wide ? 1.12 : 1.08);
-        const double tie = lines > 1.0 ? 1.005 : 1.0;
-        const double plane = (1.0 - follow + follow * lanes) * (1.0 + 8.0 / w) * (large ? lines : tie);
+        const double lines = (h * w == cells && w % 32 == 0 ? 1.0 : split) *
+                             (!cached && p.nx * word % line == 0 && w * word % line != 0 ? 1.3 : 1.0);
+        const double plane = (1.0 - follow + follow * lanes) * (1.0 + 8.0 / w) * lines;
         const double share = p.storage == hm::kF32 || p.storage == hm::kF64 ? 0.6 : 0.3;
         const bool aligned = p.nx * word % 128 == 0 && w * word % 128 == 0;
         const double narrow = 1.0 + (hm::storage_bytes(p.storage) == 2 ? 20.0 : 16.0) / w;

@@ -1,0 +1,40 @@
+"""Launch plans, chosen on the host (no device): what a domain's kernel, tile
+and chunk may be, from times measured on an MI355X."""
+import pytest
+
+import _plan
+
+
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    return _plan.build_driver("plan_driver", tmp_path_factory.mktemp("plan") / "plan_driver")
+
+
+# us a step of (tile, planes per block); each plan has to be one of those within
+# 6 % of the best
+TIMES = {
+    # the caches hold the domain: idle lanes cost little, planes a round trip each
+    ((63, 63, 63), "f64", 2): {(63, 4, 4): 38.3, (63, 3, 6): 45.1, (63, 2, 8): 53.7},
+    ((58, 209, 11), "f64", 2): {(58, 3, 4): 30.6, (58, 4, 4): 31.4, (58, 2, 6): 38.6},
+    ((268, 22, 51), "f64", 2): {(64, 4, 7): 53.7, (64, 3, 9): 61.3},
+    ((64, 64, 129), "f64", 2): {(64, 4, 9): 75.9, (64, 3, 12): 85.2},
+    ((64, 64, 129), "f32", 2): {(64, 8, 5): 39.7, (64, 6, 6): 43.5},
+    ((64, 64, 129), "f16s", 2): {(64, 8, 5): 29.2, (64, 6, 6): 32.8},
+    # rows of whole lines, beyond the caches: a tile that splits them
+    ((160, 242, 96), "f32", 1): {(64, 6, 48): 119.1, (32, 15, 32): 107.7, (54, 9, 32): 172.3},
+    ((200, 200, 100), "f64", 1): {(64, 8, 20): 260.0, (40, 12, 34): 247.0, (50, 10, 34): 321.0},
+    ((200, 200, 200), "f64", 1): {(64, 8, 40): 499.7, (40, 12, 67): 471.9, (50, 10, 67): 652.4},
+    # rows that split lines anyway keep the fitted tiles
+    ((131, 131, 131), "f16s", 2): {(44, 11, 19): 108.2, (64, 8, 27): 124.8},
+    ((131, 131, 131), "f64", 2): {(44, 5, 44): 363.9, (64, 4, 27): 407.1},
+    ((150, 150, 150), "f32", 1): {(50, 9, 30): 114.8, (50, 10, 30): 119.8, (64, 8, 38): 148.6},
+}
+
+
+@pytest.mark.parametrize("domain", TIMES, ids=lambda d: "x".join(map(str, d[0])) + "-" + d[1] + "-%d" % d[2])
+def test_planned_tile_is_near_the_best_measured(planner, domain):
+    shape, storage, ncomp = domain
+    p = _plan.plans(planner, [(shape, storage, ncomp, 1, "shan-chen")])[0]
+    times = TIMES[domain]
+    assert p.box is None
+    assert times[(*p.tile, p.zchunk)] <= 1.06 * min(times.values())
