@@ -281,6 +281,14 @@ constexpr int split_rows(bool f64, int ncomp, int c_ns)
     return ncomp == 1 ? 16 : (f64 ? 5 : (c_ns == 1 ? 10 : 8));
 }
 
+// Blocks of both sweeps in domains of at most kThinRows rows: with rows of up to
+// 64 cells a tile there has at most kThinCells, so a larger block would idle, and
+// mostly two of these fit a CU.  us a step, 512 cells / 256: 40000 x 4 x 1 in FP16 17 / 11,
+// 400 x 4 x 400 in FP16 52 / 41 and with the GS-WBS in FP32 74 / 61, 300 x 3 x 300 in
+// FP16 29 / 23; with five to seven rows 512 are the faster ones (30000 x 7 x 1 in
+// FP32 8 / 11).
+constexpr int kThinRows = 4, kThinCells = 256;
+
 // Kernel parameters in the arithmetic type.
 template <typename T>
 struct Args {

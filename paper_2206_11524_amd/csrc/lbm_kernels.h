@@ -39,6 +39,7 @@ struct Launch {
     int tile_x;   // cells per tile row (up to 64)
     int tile_y;   // rows per tile, within tile_limits
     int zchunk;   // planes per block
+    int cells;    // cells of a block of the sweep (block_cells)
     bool nt_stores;  // non-temporal stores (always in FP64)
     int bx, by, bz;  // cells per block of the box kernel (small domains); bx = 0: the sweep
     int batch_x, batch_y;  // tile in a batched launch
@@ -54,6 +55,10 @@ bool pair_layout(int storage, int ncomp, int forcing = kForcingShanChen);
 // a tile keeps to them.
 void tile_limits(const Problem& p, int* cells, int* rows);
 bool tile_supported(const Problem& p, int tile_x, int tile_y);
+
+// Cells of a block of the single-domain sweep with this tile: fewer in thin
+// domains.
+int block_cells(const Problem& p, int tile_x, int tile_y);
 
 // Bytes per stored population.
 int storage_bytes(int storage);

@@ -46,11 +46,12 @@ namespace hm {
 // A tile is any w x h cells of at most kCells with rows of up to 64 and at most
 // kRows rows, fitted to the domain like the pair sweep's (the row bound keeps the
 // staged planes within the 160 KB of LDS; lanes take the cells row by row).
-template <typename ST, int NC, int CNS>
+template <typename ST, int NC, int CNS, int CELLS = split_cells(sizeof(typename ST::T) == 8, NC)>
 struct TileShared {
     using T = typename ST::T;
-    static constexpr int kCells = split_cells(sizeof(T) == 8, NC);
-    static constexpr int kRows = split_rows(sizeof(T) == 8, NC, CNS);
+    static constexpr int kCells = CELLS;
+    static constexpr int kRows =
+        CELLS < split_cells(sizeof(T) == 8, NC) ? kThinRows : split_rows(sizeof(T) == 8, NC, CNS);
     static constexpr int kStaged = 66 * (kCells / 64 + 2);  // cells of a tile with its ring, at most
     static constexpr int LW = 66;
     static constexpr int LP = LW * (kRows + 2);
@@ -67,14 +68,14 @@ struct TileShared {
 
 // The sweep of one tile column (logical tile index L of the domain described
 // by a).  Shared by the single-domain and the batched kernels.
-template <typename ST, int NC, int CNS, int FS, bool ONE, int AUX>
+template <typename ST, int NC, int CNS, int FS, bool ONE, int AUX, int CELLS>
 __device__ __forceinline__ void step_tile(const Args<typename ST::T>& a, const typename ST::E* __restrict__ A,
                                           typename ST::E* __restrict__ B, const float* __restrict__ ns, int L,
-                                          uint32_t t, TileShared<ST, NC, CNS>& sh)
+                                          uint32_t t, TileShared<ST, NC, CNS, CELLS>& sh)
 {
     using T = typename ST::T;
     using E = typename ST::E;
-    using Shared = TileShared<ST, NC, CNS>;
+    using Shared = TileShared<ST, NC, CNS, CELLS>;
     constexpr int LW = Shared::LW, LP = Shared::LP;
     constexpr int NTC = Shared::NTC;  // threads per component
     constexpr int NT = Shared::NT;
@@ -443,16 +444,16 @@ __device__ __forceinline__ void step_tile(const Args<typename ST::T>& a, const t
 constexpr int kPairCells = 512;    // cells of a tile (one thread each), at most
 constexpr int kPairW = 64;         // cells of a tile row, at most
 constexpr int kPairH = 16;         // rows of a tile, at most
-constexpr int kPairStaged = 660;   // cells of a tile with its ring, at most (64 x 8)
 constexpr int kPairRing = 192;     // ring / n_s threads per block (three waves)
 static_assert(2 * (kPairW + 2) + 2 * kPairH <= kPairRing, "one ring cell per ring thread");
 
-template <typename ST, int CNS>
+template <typename ST, int CNS, int CELLS = kPairCells>
 struct PairShared {
     using W = typename PairWordOf<ST>::W;
     static constexpr int LW = kPairW + 2;
-    static constexpr int LP = LW * (kPairH + 2);
-    static constexpr int NT = kPairCells;
+    static constexpr int LP = LW * ((CELLS < kPairCells ? kThinRows : kPairH) + 2);
+    static constexpr int NT = CELLS;
+    static constexpr int kStaged = LW * (CELLS / kPairW + 2);  // cells of a tile with its ring, at most
     static constexpr int NB = sizeof(W) == 4 ? 2 : 1;  // planes of words held in LDS
     W hs[NB][kQ][NT];
     float rho[4][2][LP];
@@ -464,19 +465,20 @@ struct PairShared {
 #define LBM_PAIR_AHEAD 2
 #endif
 
-template <typename ST, int CNS, int FS, bool ONE, int RND, int AUX>
+template <typename ST, int CNS, int FS, bool ONE, int RND, int AUX, int CELLS>
 __device__ __forceinline__ void step_tile_pair(const Args<float>& a,
                                                const typename PairWordOf<ST>::W* __restrict__ A,
                                                typename PairWordOf<ST>::W* __restrict__ B,
                                                const float* __restrict__ ns, int L, uint32_t t,
-                                               PairShared<ST, CNS>& sh)
+                                               PairShared<ST, CNS, CELLS>& sh)
 {
     using T = float;
     using W = typename PairWordOf<ST>::W;
-    constexpr int LW = PairShared<ST, CNS>::LW, LP = PairShared<ST, CNS>::LP;
-    constexpr int NT = kPairCells;
+    using Shared = PairShared<ST, CNS, CELLS>;
+    constexpr int LW = Shared::LW, LP = Shared::LP;
+    constexpr int NT = CELLS;
     constexpr int NR = kPairRing;
-    constexpr int NSR = (kPairStaged + NR - 1) / NR;  // n_s cells staged per ring thread and plane
+    constexpr int NSR = (Shared::kStaged + NR - 1) / NR;  // n_s cells staged per ring thread and plane
     static_assert(NT % 64 == 0, "the roles must fill whole waves");
     auto& s_rho = sh.rho;
     auto& s_ns = sh.ns;
@@ -736,26 +738,32 @@ __device__ __forceinline__ void step_tile_pair(const Args<float>& a,
 }
 
 template <typename ST, int NC, int FS = kForcingShanChen>
-constexpr int kThreads = kPair<ST, NC, FS> ? kPairCells + kPairRing : NC * split_cells(sizeof(typename ST::T) == 8, NC);
+constexpr int kBlockCells = kPair<ST, NC, FS> ? kPairCells : split_cells(sizeof(typename ST::T) == 8, NC);
 
-template <typename ST, int NC, int CNS, int FS, bool ONE, int RND, int AUX>
-__global__ __launch_bounds__((kThreads<ST, NC, FS>)) void k_step(Args<typename ST::T> a,
-                                                                    const typename ST::E* __restrict__ A,
-                                                                    typename ST::E* __restrict__ B,
-                                                                    const float* __restrict__ ns)
+template <typename ST, int NC, int FS = kForcingShanChen, int CELLS = kBlockCells<ST, NC, FS>>
+constexpr int kThreads = kPair<ST, NC, FS> ? CELLS + kPairRing : NC * CELLS;
+
+// CELLS: cells of a block, kBlockCells or, in thin domains, kThinCells.
+template <typename ST, int NC, int CNS, int FS, bool ONE, int RND, int AUX, int CELLS>
+__global__ __launch_bounds__((kThreads<ST, NC, FS, CELLS>)) void k_step(Args<typename ST::T> a,
+                                                                        const typename ST::E* __restrict__ A,
+                                                                        typename ST::E* __restrict__ B,
+                                                                        const float* __restrict__ ns)
 {
     // One block fits a CU, two with one component in FP32 arithmetic (77 KB of
-    // LDS): a round is 256 or 512 blocks.  Runs per round instead of one run of
-    // the whole grid: 181^3 in FP64, 690 blocks, 948 us against 1050.
-    const int L = xcd_tile(blockIdx.x, gridDim.x, NC == 1 && sizeof(typename ST::T) == 4 ? 512 : 256);
+    // LDS) and, but for two n_s fields with the GS-WBS, with the smaller blocks of
+    // thin domains: a round is 256 or 512 blocks.  Runs per round instead of one run of the whole grid: 181^3 in FP64,
+    // 690 blocks, 948 us against 1050.
+    constexpr bool TWO = CELLS < kBlockCells<ST, NC, FS> || (NC == 1 && sizeof(typename ST::T) == 4);
+    const int L = xcd_tile(blockIdx.x, gridDim.x, TWO ? 512 : 256);
     if constexpr (kPair<ST, NC, FS>) {
         using W = typename PairWordOf<ST>::W;
-        __shared__ PairShared<ST, CNS> sh;
-        step_tile_pair<ST, CNS, FS, ONE, RND, AUX>(a, reinterpret_cast<const W*>(A), reinterpret_cast<W*>(B), ns, L,
-                                                      a.t, sh);
+        __shared__ PairShared<ST, CNS, CELLS> sh;
+        step_tile_pair<ST, CNS, FS, ONE, RND, AUX, CELLS>(a, reinterpret_cast<const W*>(A), reinterpret_cast<W*>(B), ns,
+                                                          L, a.t, sh);
     } else {
-        __shared__ TileShared<ST, NC, CNS> sh;
-        step_tile<ST, NC, CNS, FS, ONE, AUX>(a, A, B, ns, L, a.t, sh);
+        __shared__ TileShared<ST, NC, CNS, CELLS> sh;
+        step_tile<ST, NC, CNS, FS, ONE, AUX, CELLS>(a, A, B, ns, L, a.t, sh);
     }
 }
 
@@ -821,12 +829,12 @@ __global__ __launch_bounds__((kThreads<ST, NC>)) void k_step_batch(const char* _
             const uint32_t tk = e.a.t + static_cast<uint32_t>(k);
             if (sizeof(E) == 2 && e.a.sr)
                 step_tile_pair<ST, CNS, kForcingShanChen, false, sizeof(E) == 2 ? kRoundStochastic : kRoundNearest,
-                               AUX>(e.a, src, dst, e.ns, w - e.tile_begin, tk, sh);
+                               AUX, kPairCells>(e.a, src, dst, e.ns, w - e.tile_begin, tk, sh);
             else
-                step_tile_pair<ST, CNS, kForcingShanChen, false, kRoundNearest, AUX>(e.a, src, dst, e.ns,
-                                                                                     w - e.tile_begin, tk, sh);
+                step_tile_pair<ST, CNS, kForcingShanChen, false, kRoundNearest, AUX, kPairCells>(
+                    e.a, src, dst, e.ns, w - e.tile_begin, tk, sh);
         } else
-            step_tile<ST, NC, CNS, kForcingShanChen, false, AUX>(
+            step_tile<ST, NC, CNS, kForcingShanChen, false, AUX, kBlockCells<ST, NC>>(
                 e.a, static_cast<const E*>(e.buf[cur]), static_cast<E*>(const_cast<void*>(e.buf[1 - cur])), e.ns,
                 w - e.tile_begin, e.a.t + static_cast<uint32_t>(k), sh);
     }
@@ -1282,7 +1290,6 @@ bool pair_layout(int storage, int ncomp, int forcing)
     return ((storage == kF32 && forcing != kForcingGuo) || storage == kF16 || storage == kBF16) && ncomp == 2;
 }
 
-
 void tile_limits(const Problem& p, int* cells, int* rows)
 {
     const bool pair = pair_layout(p.storage, p.ncomp, p.forcing);
@@ -1295,6 +1302,13 @@ bool tile_supported(const Problem& p, int tx, int ty)
     int cells, rows;
     tile_limits(p, &cells, &rows);
     return tx >= 1 && ty >= 1 && tx <= 64 && ty <= rows && tx * ty <= cells;
+}
+
+int block_cells(const Problem& p, int tx, int ty)
+{
+    int cells, rows;
+    tile_limits(p, &cells, &rows);
+    return p.ny <= kThinRows && ty <= kThinRows && tx * ty <= kThinCells ? std::min(cells, kThinCells) : cells;
 }
 
 int storage_bytes(int storage)
@@ -1323,16 +1337,22 @@ static hipError_t step_t(const Problem& p, const Launch& l, int64_t t, const voi
     a.nzc = (p.nz + l.zchunk - 1) / l.zchunk;
     a.t = static_cast<uint32_t>(t);
     const int nblocks = a.ntx * a.nty * a.nzc;
-    // one instance per store policy (FP64 and one plane keep non-temporal
-    // stores), and of the pair kernel per rounding mode; the split kernels
-    // branch on it (their two store sequences are alike)
-    auto go = [&](auto rnd, auto aux) {
-        hipLaunchKernelGGL((k_step<ST, NC, CNS, FS, ONE, decltype(rnd)::value, decltype(aux)::value>), dim3(nblocks),
-                           dim3(kThreads<ST, NC, FS>), 0, st, a, static_cast<const E*>(A), static_cast<E*>(B), ns);
+    // one instance per block size and store policy (FP64 and one plane keep
+    // non-temporal stores), and of the pair kernel per rounding mode; the split
+    // kernels branch on it (their two store sequences are alike)
+    constexpr int CELLS = kBlockCells<ST, NC, FS>;
+    auto go = [&](auto rnd, auto aux, auto cells) {
+        constexpr int NB = decltype(cells)::value;
+        hipLaunchKernelGGL((k_step<ST, NC, CNS, FS, ONE, decltype(rnd)::value, decltype(aux)::value, NB>),
+                           dim3(nblocks), dim3(kThreads<ST, NC, FS, NB>), 0, st, a, static_cast<const E*>(A),
+                           static_cast<E*>(B), ns);
     };
     using Nt = std::integral_constant<int, kNT>;
     using Cached = std::integral_constant<int, ONE || sizeof(E) == 8 ? kNT : 0>;
-    auto policy = [&](auto rnd) { l.nt_stores ? go(rnd, Nt{}) : go(rnd, Cached{}); };
+    using Full = std::integral_constant<int, CELLS>;
+    using Thin = std::integral_constant<int, std::min(CELLS, kThinCells)>;
+    auto block = [&](auto rnd, auto aux) { l.cells < CELLS ? go(rnd, aux, Thin{}) : go(rnd, aux, Full{}); };
+    auto policy = [&](auto rnd) { l.nt_stores ? block(rnd, Nt{}) : block(rnd, Cached{}); };
     if constexpr (kPair<ST, NC, FS>) {
         // FP32 rounds to nearest
         if (sizeof(E) == 2 && p.stochastic)
@@ -1349,7 +1369,8 @@ static hipError_t step_fs(const Problem& p, const Launch& l, int64_t t, const vo
                           hipStream_t st)
 {
     constexpr int SC = kForcingShanChen, GUO = kForcingGuo;
-    if (!tile_supported(p, l.tile_x, l.tile_y)) return hipErrorInvalidValue;
+    if (!tile_supported(p, l.tile_x, l.tile_y) || l.cells != block_cells(p, l.tile_x, l.tile_y))
+        return hipErrorInvalidValue;
     const bool one = p.nz == 1;
     if (p.forcing == GUO)
         return one ? step_t<ST, NC, CNS, GUO, true>(p, l, t, A, B, ns, st)

@@ -116,8 +116,9 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     const bool given = (env_x || env_y) && hm::tile_supported(p, l.tile_x, l.tile_y);
     if (!given) {
         l.tile_x = 64;
-        l.tile_y = cells / 64;
+        l.tile_y = std::min(cells / 64, p.ny);
     }
+    l.cells = hm::block_cells(p, l.tile_x, l.tile_y);
     const int64_t ncu = std::max(cus, 1);
     const int64_t word = hm::storage_bytes(p.storage) * (pair ? 2 : 1);
     auto part = [](int n, int k) { return (n + k - 1) / k; };
@@ -176,9 +177,10 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     auto consider = [&](int w, int h) {
         const int64_t cols = static_cast<int64_t>((p.nx + w - 1) / w) * ((p.ny + h - 1) / h);
         const double lanes = static_cast<double>(p.nx) * p.ny / (static_cast<double>(cols) * cells);
-        const double lines = (h * w == cells && w % 32 == 0 ? 1.0 : split) *
+        const double own = lanes * cells / l.cells;
+        const double lines = (h * w == l.cells && w % 32 == 0 ? 1.0 : split) *
                              (!cached && p.nx * word % line == 0 && w * word % line != 0 ? 1.3 : 1.0);
-        const double plane = (1.0 - follow + follow * lanes) * (1.0 + 8.0 / w) * lines;
+        const double plane = (1.0 - follow + follow * own) * (1.0 + 8.0 / w) * lines;
         const double share = p.storage == hm::kF32 || p.storage == hm::kF64 ? 0.6 : 0.3;
         const bool aligned = p.nx * word % 128 == 0 && w * word % 128 == 0;
         const double narrow = 1.0 + (hm::storage_bytes(p.storage) == 2 ? 20.0 : 16.0) / w;

@@ -10,7 +10,7 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 KNOBS = ("LBM_BOX", "LBM_TILE_X", "LBM_TILE_Y", "LBM_ZCHUNK", "LBM_BATCH_TILE_X", "LBM_BATCH_TILE_Y")
 FORCING = {"shan-chen": 0, "guo": 1}
 
-Plan = collections.namedtuple("Plan", "box tile zchunk nt group server")
+Plan = collections.namedtuple("Plan", "box tile zchunk nt group server cells")
 
 
 def build_driver(name, out):
@@ -41,4 +41,4 @@ def plans(exe, domains, env=None):
                    for s, st, nc, cn, fo in domains)
     out = [tuple(map(int, line.split())) for line in run_driver(exe, text=text, env=env)]
     assert len(out) == len(domains)
-    return [Plan(v[0:3] if v[0] else None, v[3:5], v[5], bool(v[6]), v[7:9], v[9:11]) for v in out]
+    return [Plan(v[0:3] if v[0] else None, v[3:5], v[5], bool(v[6]), v[7:9], v[9:11], v[11]) for v in out]

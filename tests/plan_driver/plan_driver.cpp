@@ -1,6 +1,6 @@
 // Prints the launch plan of each domain on standard input ("nx ny nz storage
 // ncomp c_ns forcing" a line) for a device of 256 CUs: box, tile and chunk of
-// the sweep, store policy, tile in a group, tile in a server.  Host code only.
+// the sweep, store policy, tile in a group, tile in a server, cells of a block.  Host code only.
 #include <cstdio>
 
 #include "lbm_internal.h"
@@ -15,8 +15,8 @@ int main()
         if (hm_rt::validate(&d, &p)) return 1;
         const hm::Problem q = hm_rt::make_problem(&d, &p);
         const hm::Launch l = hm_rt::choose_launch(q, 256, false), s = hm_rt::choose_launch(q, 256, true);
-        std::printf("%d %d %d %d %d %d %d %d %d %d %d\n", l.bx, l.by, l.bz, l.tile_x, l.tile_y, l.zchunk,
-                    l.nt_stores ? 1 : 0, l.batch_x, l.batch_y, s.batch_x, s.batch_y);
+        std::printf("%d %d %d %d %d %d %d %d %d %d %d %d\n", l.bx, l.by, l.bz, l.tile_x, l.tile_y, l.zchunk,
+                    l.nt_stores ? 1 : 0, l.batch_x, l.batch_y, s.batch_x, s.batch_y, l.cells);
     }
     return 0;
 }

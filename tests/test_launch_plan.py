@@ -38,3 +38,21 @@ def test_planned_tile_is_near_the_best_measured(planner, domain):
     times = TIMES[domain]
     assert p.box is None
     assert times[(*p.tile, p.zchunk)] <= 1.06 * min(times.values())
+
+
+@pytest.mark.parametrize("storage,ncomp,c_ns,forcing", [("f64", 1, 1, "shan-chen"), ("f32", 1, 1, "guo"),
+                                                        ("f32", 2, 2, "guo"), ("f32", 2, 1, "shan-chen"),
+                                                        ("f16s", 2, 2, "guo"), ("bf16s", 1, 1, "shan-chen")])
+def test_thin_domains_take_small_blocks(planner, storage, ncomp, c_ns, forcing):
+    """Four rows fill 256 lanes of a block at most; beyond them 512 are the
+    faster ones."""
+    fmt = (storage, ncomp, c_ns, forcing)
+    thin = [((nx, ny, nz), *fmt) for nx, nz in ((40000, 1), (400, 400), (100, 2000)) for ny in (1, 2, 3, 4)]
+    for p in _plan.plans(planner, thin, env=dict(LBM_BOX="0")):
+        assert p.cells == 256 and p.tile[1] <= 4
+    for p in _plan.plans(planner, [((40000, 5, 1), *fmt), ((400, 7, 400), *fmt)], env=dict(LBM_BOX="0")):
+        assert p.cells == 512
+    # a tile that does not fit the small block keeps the large one
+    for ty, cells in ((4, 256), (8, 512)):
+        p = _plan.plans(planner, [((400, 4, 400), *fmt)], env=dict(LBM_TILE_X=64, LBM_TILE_Y=ty))[0]
+        assert (p.tile, p.cells) == ((64, ty), cells)
