@@ -39,7 +39,7 @@ struct BoxShared {
     T j[PAIR || NC == 1 ? 1 : 2][3][PAIR || NC == 1 ? 1 : kBoxMaxThreads / 2];
 };
 
-template <typename ST, int NC, int CNS, int FS, int RND>
+template <typename ST, int NC, int CNS, int FS, int RND, int AUX>
 __global__ __launch_bounds__(kBoxMaxThreads) void k_step_box(Args<typename ST::T> a, BoxDims b,
                                                              const typename ST::E* __restrict__ A,
                                                              typename ST::E* __restrict__ B,
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kBoxMaxThreads) void k_step_box(Args<typename ST::T
         pair_collide<ST, CNS, FS, RND>(
             geo, a, rbits, t_key, cell, me, rho0 - lxy, rho0, rho0 + lxy, ns0 - lxy, ns0, ns0 + lxy, jm,
             [&](int i) { return e[i]; },
-            [&](int i, W v) { raw_store<kNT>(v, rb, own, static_cast<uint32_t>(i) * dir_bytes); });
+            [&](int i, W v) { raw_store<AUX>(v, rb, own, static_cast<uint32_t>(i) * dir_bytes); });
     } else {
         T h[kQ];
         if (act) {
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(kBoxMaxThreads) void k_step_box(Args<typename ST::T
         const rsrc_t rb = make_rsrc(reinterpret_cast<W*>(B) + s * cstride, all_bytes);
         split_collide<ST, NC, CNS, FS>(
             geo, a, s, t_key, cell, me, rho0 - lxy, rho0, rho0 + lxy, ns0 - lxy, ns0, ns0 + lxy, jc, h,
-            [&](int i, W v) { raw_store<kNT>(v, rb, own, static_cast<uint32_t>(i) * dir_bytes); });
+            [&](int i, W v) { raw_store<AUX>(v, rb, own, static_cast<uint32_t>(i) * dir_bytes); });
     }
 }
 
@@ -295,6 +295,21 @@ bool choose_box(const Problem& p, int cus, int* bx, int* by, int* bz)
     return best >= 0.0;
 }
 
+// While both buffers stay in the L2 caches (4 MB in each of 8 XCDs), stores past
+// them cost nothing or save up to a tenth: the lines that they would fill are
+// those that the next step reads.  Beyond, the rows of a box start and end inside
+// lines, which two boxes write in parts, and cached stores merge them.  Cached
+// against non-temporal, us a step: 41^3 in FP32 (10 MB a buffer) 9.3 / 8.7, 57^3 in
+// FP16 (14 MB) 15.2 / 17.3, 53 x 148 x 28 in FP16 (17 MB) 16.5 / 20.4, 42^3 in FP64
+// (23 MB) 17.9 / 20.6; one component crosses later: 247 x 111 x 8 in FP32 (17 MB)
+// 11.6 / 10.1, 101 x 118 x 21 (19 MB) 11.2 / 11.1, 268 x 22 x 51 (23 MB) 12.0 / 13.3,
+// 261 x 95 x 19 (36 MB) 17.1 / 22.5, in FP64 (72 MB) 31.9 / 38.4.
+bool box_nt_stores(const Problem& p)
+{
+    const int64_t state = p.N * kQ * storage_bytes(p.storage) * p.ncomp;
+    return state < (p.ncomp == 2 ? 14000000 : 22000000);
+}
+
 template <typename ST, int NC, int CNS, int FS>
 static hipError_t box_t(const Problem& p, const Launch& l, int64_t t, const void* A, void* B, const float* ns,
                         hipStream_t st)
@@ -312,14 +327,17 @@ static hipError_t box_t(const Problem& p, const Launch& l, int64_t t, const void
     b.own_pad = 64 * whole_waves(b.bx * b.by * b.bz);
     b.halo_pad = 64 * whole_waves(box_halo(p, b.bx, b.by, b.bz));
     const int threads = (PAIR ? 1 : NC) * (b.own_pad + b.halo_pad);
-    constexpr int SR = sizeof(E) == 2 && PAIR ? kRoundStochastic : kRoundNearest;
     const dim3 grid(static_cast<unsigned>(b.nbx) * b.nby * nbz);
-    if (p.stochastic)
-        hipLaunchKernelGGL((k_step_box<ST, NC, CNS, FS, SR>), grid, dim3(threads), 0, st, a, b,
-                           static_cast<const E*>(A), static_cast<E*>(B), ns);
-    else
-        hipLaunchKernelGGL((k_step_box<ST, NC, CNS, FS, kRoundNearest>), grid, dim3(threads), 0, st, a, b,
-                           static_cast<const E*>(A), static_cast<E*>(B), ns);
+    auto go = [&](auto rnd, auto aux) {
+        hipLaunchKernelGGL((k_step_box<ST, NC, CNS, FS, decltype(rnd)::value, decltype(aux)::value>), grid,
+                           dim3(threads), 0, st, a, b, static_cast<const E*>(A), static_cast<E*>(B), ns);
+    };
+    auto policy = [&](auto rnd) {
+        l.nt_stores ? go(rnd, std::integral_constant<int, kNT>{}) : go(rnd, std::integral_constant<int, 0>{});
+    };
+    constexpr int SR = sizeof(E) == 2 && PAIR ? kRoundStochastic : kRoundNearest;
+    if (p.stochastic) policy(std::integral_constant<int, SR>{});
+    else policy(std::integral_constant<int, kRoundNearest>{});
     return hipGetLastError();
 }
 

@@ -40,7 +40,7 @@ struct Launch {
     int tile_y;   // rows per tile, within tile_limits
     int zchunk;   // planes per block
     int cells;    // cells of a block of the sweep (block_cells)
-    bool nt_stores;  // non-temporal stores (always in FP64)
+    bool nt_stores;  // non-temporal stores (always in the sweep in FP64)
     int bx, by, bz;  // cells per block of the box kernel (small domains); bx = 0: the sweep
     int batch_x, batch_y;  // tile in a batched launch
 };
@@ -74,6 +74,9 @@ bool box_fits(const Problem& p, int bx, int by, int bz);
 
 // The box for a domain small enough to gain from it; false: use the sweep.
 bool choose_box(const Problem& p, int cus, int* bx, int* by, int* bz);
+
+// Store policy of the box kernel: non-temporal stores, or cached ones.
+bool box_nt_stores(const Problem& p);
 
 hipError_t launch_step_box(const Problem& p, const Launch& l, int64_t t, const void* A, void* B,
                            const float* ns, hipStream_t s);

@@ -56,3 +56,13 @@ def test_thin_domains_take_small_blocks(planner, storage, ncomp, c_ns, forcing):
     for ty, cells in ((4, 256), (8, 512)):
         p = _plan.plans(planner, [((400, 4, 400), *fmt)], env=dict(LBM_TILE_X=64, LBM_TILE_Y=ty))[0]
         assert (p.tile, p.cells) == ((64, ty), cells)
+
+
+def test_box_stores_are_cached_beyond_the_l2(planner):
+    """Domains of the box kernel, us a step with cached / non-temporal stores."""
+    cached = [((261, 95, 19), "f32", 1), ((261, 95, 19), "f64", 1), ((57, 57, 57), "f16s", 2),  # 17 / 22, 32 / 38, 15 / 17
+              ((42, 42, 42), "f64", 2)]  # 18 / 21
+    nt = [((41, 41, 41), "f32", 2), ((247, 111, 8), "f32", 1), ((36, 36, 36), "f32", 2)]  # 9.3 / 8.7, 12 / 10, 8.1 / 7.2
+    for d, want in [(d, False) for d in cached] + [(d, True) for d in nt]:
+        p = _plan.plans(planner, [(*d, 1, "shan-chen")])[0]
+        assert p.box and p.nt is want, d
