@@ -223,7 +223,7 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
             }
         }
     }
-    if (best < 0.0) consider(l.tile_x, l.tile_y);  // as given, or one plane
+    if (best < 0.0 && batch_best < 0.0) consider(l.tile_x, l.tile_y);  // as given, or one plane
     // Non-temporal stores keep the written state out of the caches' way, but
     // where a tile's rows start or end inside a 128-byte line the two tiles that
     // share it each write part of it, and only a cached line is merged before it

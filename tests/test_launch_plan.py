@@ -66,3 +66,15 @@ def test_box_stores_are_cached_beyond_the_l2(planner):
     for d, want in [(d, False) for d in cached] + [(d, True) for d in nt]:
         p = _plan.plans(planner, [(*d, 1, "shan-chen")])[0]
         assert p.box and p.nt is want, d
+
+
+def test_served_and_grouped_domains_have_the_same_tile(planner):
+    """Cubes of edge 2 to 192 and flat, thin and uneven domains, in every
+    format of the batched kernel."""
+    shapes = [(e, e, e) for e in range(2, 193)]
+    shapes += [(x, y, z) for x in (5, 17, 40, 63, 100, 127) for y in (3, 12, 40, 77) for z in (1, 6, 50)]
+    fmts = [(st, nc, cn, "shan-chen") for st in ("f64", "f32", "f16s", "bf16s") for nc, cn in ((1, 1), (2, 1), (2, 2))]
+    domains = [(s, *f) for s in shapes for f in fmts]
+    for d, p in zip(domains, _plan.plans(planner, domains)):
+        assert p.group == p.server, d
+        assert p.group[0] <= max(d[0][0], 64)
