@@ -171,28 +171,52 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     const double follow = cached ? 0.15 : 0.3;
     const double split = f64 ? (p.ncomp == 2 && p.N > 1500000 ? 1.12 : 1.03) : (p.N > 6000000 ? 1.08 : 1.005);
     const int64_t line = f64 ? 64 : 128;
-    double best = -1.0, batch_best = -1.0;
+    auto each_tile = [&](auto&& consider) {
+        const int k0 = part(p.nx, 64);
+        for (int k = k0 - 1; k <= k0 + 3; ++k) {
+            const int w = k < k0 ? 64 : part(p.nx, k);
+            if (w > p.nx || (k > k0 && w < 24)) continue;
+            int h = part(p.ny, part(p.ny, std::min(std::min(rows, cells / w), p.ny)));
+            for (;;) {
+                consider(w, h);
+                if (h == 1 || h * w < cells / 2) break;
+                h = part(p.ny, part(p.ny, h - 1));
+            }
+        }
+    };
+    auto columns = [&](int w, int h) { return static_cast<int64_t>(part(p.nx, w)) * part(p.ny, h); };
+    auto lanes_of = [&](int64_t cols, int block) {
+        return static_cast<double>(p.nx) * p.ny / (static_cast<double>(cols) * block);
+    };
+    // the tile in batched launches (one plane: whole rows)
     l.batch_x = 64;
-    l.batch_y = cells / 64;
+    l.batch_y = std::min(cells / 64, p.ny);
+    double batch_best = -1.0;
+    if (p.nz > 1)
+        each_tile([&](int w, int h) {
+            const int64_t cols = columns(w, h);
+            const double lanes = lanes_of(cols, cells);
+            const double share = p.storage == hm::kF32 || p.storage == hm::kF64 ? 0.6 : 0.3;
+            const bool aligned = p.nx * word % 128 == 0 && w * word % 128 == 0;
+            const double narrow = 1.0 + (hm::storage_bytes(p.storage) == 2 ? 20.0 : 16.0) / w;
+            const double column =
+                static_cast<double>(cols) * (1.0 - share + share * lanes) * narrow * (aligned ? 1.0 : 1.08);
+            const bool splits = p.nx * word % 128 == 0 && w * word % 128 != 0;
+            if (!splits && (batch_best < 0.0 || column < batch_best)) {
+                batch_best = column;
+                l.batch_x = w;
+                l.batch_y = h;
+            }
+        });
+    if (batched) return l;
+    // the tile and chunk of the sweep
+    double best = -1.0;
     auto consider = [&](int w, int h) {
-        const int64_t cols = static_cast<int64_t>((p.nx + w - 1) / w) * ((p.ny + h - 1) / h);
-        const double lanes = static_cast<double>(p.nx) * p.ny / (static_cast<double>(cols) * cells);
-        const double own = lanes * cells / l.cells;
+        const int64_t cols = columns(w, h);
+        const double lanes = lanes_of(cols, l.cells);
         const double lines = (h * w == l.cells && w % 32 == 0 ? 1.0 : split) *
                              (!cached && p.nx * word % line == 0 && w * word % line != 0 ? 1.3 : 1.0);
-        const double plane = (1.0 - follow + follow * own) * (1.0 + 8.0 / w) * lines;
-        const double share = p.storage == hm::kF32 || p.storage == hm::kF64 ? 0.6 : 0.3;
-        const bool aligned = p.nx * word % 128 == 0 && w * word % 128 == 0;
-        const double narrow = 1.0 + (hm::storage_bytes(p.storage) == 2 ? 20.0 : 16.0) / w;
-        const double column =
-            static_cast<double>(cols) * (1.0 - share + share * lanes) * narrow * (aligned ? 1.0 : 1.08);
-        const bool splits = p.nx * word % 128 == 0 && w * word % 128 != 0;
-        if (!splits && (batch_best < 0.0 || column < batch_best)) {
-            batch_best = column;
-            l.batch_x = w;
-            l.batch_y = h;
-        }
-        if (batched) return;
+        const double plane = (1.0 - follow + follow * lanes) * (1.0 + 8.0 / w) * lines;
         const int64_t tiles16 = cols * ((p.nz + 15) / 16);
         const int min_chunk = tiles16 >= 2 * ncu ? 16 : 4;
         // the distinct chunk lengths of even parts of nz, longest first
@@ -210,20 +234,8 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
             if (z < min_chunk) break;
         }
     };
-    if (!given && p.nz > 1) {
-        const int k0 = part(p.nx, 64);
-        for (int k = k0 - 1; k <= k0 + 3; ++k) {
-            const int w = k < k0 ? 64 : part(p.nx, k);
-            if (w > p.nx || (k > k0 && w < 24)) continue;
-            int h = part(p.ny, part(p.ny, std::min(std::min(rows, cells / w), p.ny)));
-            for (;;) {
-                consider(w, h);
-                if (h == 1 || h * w < cells / 2) break;
-                h = part(p.ny, part(p.ny, h - 1));
-            }
-        }
-    }
-    if (best < 0.0 && batch_best < 0.0) consider(l.tile_x, l.tile_y);  // as given, or one plane
+    if (given || p.nz == 1) consider(l.tile_x, l.tile_y);
+    else each_tile(consider);
     // Non-temporal stores keep the written state out of the caches' way, but
     // where a tile's rows start or end inside a 128-byte line the two tiles that
     // share it each write part of it, and only a cached line is merged before it

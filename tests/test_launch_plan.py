@@ -78,3 +78,13 @@ def test_served_and_grouped_domains_have_the_same_tile(planner):
     for d, p in zip(domains, _plan.plans(planner, domains)):
         assert p.group == p.server, d
         assert p.group[0] <= max(d[0][0], 64)
+
+
+@pytest.mark.parametrize("tile", [dict(LBM_TILE_X=32), dict(LBM_TILE_Y=2), dict(LBM_TILE_X=20, LBM_TILE_Y=5)],
+                         ids=lambda e: "-".join("%s=%d" % i for i in e.items()))
+def test_sweep_tile_settings_stay_out_of_groups_and_servers(planner, tile):
+    domains = [(s, st, nc, 1, "shan-chen") for s in ((40, 40, 40), (131, 50, 20), (96, 96, 96), (300, 50, 1))
+               for st in ("f64", "f32", "f16s") for nc in (1, 2)]
+    for d, p, q in zip(domains, _plan.plans(planner, domains), _plan.plans(planner, domains, env=tile)):
+        assert (p.group, p.server) == (q.group, q.server), d
+        assert q.tile[0] == tile.get("LBM_TILE_X", 64) and q.box is None
