@@ -381,8 +381,9 @@ typedef struct {
     int32_t storage;           /* lbm_storage of every request                               */
     int32_t ncomp, c_ns;       /* component and n_s-field counts of every request            */
     int64_t max_cells;         /* largest accepted domain (sizes the shared scratch)         */
-    int32_t tile_x, tile_y;    /* tile of the batched kernel; 0: chosen per domain, or 64 x 8
-                                  (FP64, one component)                                    */
+    int32_t tile_x, tile_y;    /* tile of the batched kernel: 64 x 8, or 32 x 8 with one component
+                                  or in FP64 (where two components take 64 x 4 and 32 x 5);
+                                  both 0: chosen per domain                                */
     int32_t policy;            /* lbm_serve_policy                                           */
     int32_t pad;               /* must be 0                                                  */
     int64_t run_cells;         /* SHORTEST_FIRST: cells stepped per tick at least; 0: 2^24   */

@@ -37,8 +37,8 @@ class BatchRunner {
   public:
     ~BatchRunner() { release(); }
 
-    // tile_x, tile_y: tile of every domain that can take it, 0: each domain's own
-    // (Launch::batch_x, batch_y).  nt: the store policy whose graphs are captured
+    // tile_x, tile_y: tile of every domain, of as many of its rows as the format's
+    // tiles hold; 0: each domain's own (Launch::batch_x, batch_y).  nt: the store policy whose graphs are captured
     // now (the other's when a tick needs them).
     int init(int storage, int ncomp, int c_ns, int tile_x, int tile_y, int max_domains, int k_graph, bool nt,
              hipStream_t st)
@@ -133,9 +133,11 @@ class BatchRunner {
         int64_t cols = 0, tiles16 = 0;
         int64_t whole = 0;  // cells in whole lines, less the others
         for (hm::BatchDomain& b : balanced_) {
-            if (!own_tiles_ && hm::tile_supported(b.prob, tx_, ty_)) {
+            if (!own_tiles_) {
+                int cells, rows;
+                hm::tile_limits(b.prob, &cells, &rows);
                 b.tile_x = tx_;
-                b.tile_y = ty_;
+                b.tile_y = std::min(ty_, std::min(rows, cells / tx_));
             }
             whole += whole_lines(b) ? b.prob.N : -b.prob.N;
             const int64_t c = columns(b);

@@ -158,7 +158,7 @@ size_t batch_table_bytes(int storage, int max_domains);
 int batch_encode(int storage, const BatchDomain* d, int n, void* host);
 
 // Tile shapes that may be asked of the batched kernel (64 x 8, and 32 x 8 in
-// the split layout).
+// the split layout); rows beyond tile_limits are left out.
 bool batch_tile_supported(int storage, int ncomp, int tile_x, int tile_y);
 
 // Blocks of the batched kernel that fit one CU at once (registers, LDS); at
