@@ -3,8 +3,8 @@
 //
 // Both drive the batched step kernel through a BatchRunner: two device copies
 // of the domain table (double-buffered so the host can encode tick k+1 while
-// tick k still reads its table), pinned staging, and two captured HIP graphs
-// of K launches (one per table copy).  A launch k advances every domain whose
+// tick k still reads its table), pinned staging, and captured HIP graphs of K
+// launches (one per table copy and store policy).  A launch k advances every domain whose
 // step count for the tick exceeds k, so domains with different remaining
 // budgets share one graph.
 #include <hip/hip_runtime.h>
@@ -38,10 +38,11 @@ class BatchRunner {
     ~BatchRunner() { release(); }
 
     // tile_x, tile_y: tile of every domain, of as many of its rows as the format's
-    // tiles hold; 0: each domain's own (Launch::batch_x, batch_y).  nt: the store policy whose graphs are captured
-    // now (the other's when a tick needs them).
-    int init(int storage, int ncomp, int c_ns, int tile_x, int tile_y, int max_domains, int k_graph, bool nt,
-             hipStream_t st)
+    // tiles hold; 0: each domain's own (Launch::batch_x, batch_y).  fixed: the
+    // domains of every run, if they are known (a group's): only the graphs of
+    // their store policy are captured.
+    int init(int storage, int ncomp, int c_ns, int tile_x, int tile_y, int max_domains, int k_graph,
+             const std::vector<hm::BatchDomain>& fixed, hipStream_t st)
     {
         own_tiles_ = !tile_x && !tile_y;
         if (!tile_x) tile_x = 64;
@@ -76,35 +77,49 @@ class BatchRunner {
         }
         HIP_TRY(hipEventCreate(&t0_));
         HIP_TRY(hipEventCreate(&t1_));
-        graphs_ok_ = true;
-        capture(nt);
+        // graphs are captured here only: in a run the host work would fall into a
+        // timed and served step, and the stream may be the caller's
+        balanced_ = fixed;
+        const bool nt = storage == hm::kF64 || fit_tiles();  // FP64 has one policy
+        if (storage != hm::kF64 && (fixed.empty() || !nt)) capture(false);
+        if (fixed.empty() || nt) capture(true);
         return LBM_OK;
     }
 
-    // Graphs of kmax launches with one store policy, one per table copy.
+    // Graphs of kmax launches with one store policy, one per table copy; a run
+    // whose graph could not be captured launches its steps one by one.
     void capture(bool nt)
     {
-        hipGraphExec_t(&exec)[2] = exec_[nt ? 1 : 0];
-        for (int j = 0; j < 2 && graphs_ok_; ++j) {
+        for (int j = 0; j < 2; ++j) {
+            hipGraphExec_t& exec = exec_[nt ? 1 : 0][j];
             hipGraph_t g = nullptr;
-            if (hipStreamBeginCapture(stream_, hipStreamCaptureModeRelaxed) != hipSuccess) {
-                graphs_ok_ = false;
-                break;
-            }
+            if (hipStreamBeginCapture(stream_, hipStreamCaptureModeRelaxed) != hipSuccess) continue;
             bool ok = true;
             for (int k = 0; k < kmax_; ++k)
                 ok = ok && hm::launch_step_batch(storage_, ncomp_, c_ns_, dev_[j], k, grid_, nt, stream_) ==
                                hipSuccess;
-            if (hipStreamEndCapture(stream_, &g) != hipSuccess || !ok || !g) {
-                graphs_ok_ = false;
-                if (g) (void)hipGraphDestroy(g);
-                (void)hipGetLastError();
-                break;
-            }
-            if (hipGraphInstantiate(&exec[j], g, nullptr, nullptr, 0) != hipSuccess) graphs_ok_ = false;
-            (void)hipGraphDestroy(g);
+            ok = hipStreamEndCapture(stream_, &g) == hipSuccess && ok && g;
+            if (ok && hipGraphInstantiate(&exec, g, nullptr, nullptr, 0) != hipSuccess) exec = nullptr;
+            if (g) (void)hipGraphDestroy(g);
         }
         (void)hipGetLastError();
+    }
+
+    // Gives the domains of balanced_ their tiles; returns the launches' store
+    // policy.
+    bool fit_tiles()
+    {
+        int64_t whole = 0;  // cells in whole lines, less the others
+        for (hm::BatchDomain& b : balanced_) {
+            if (!own_tiles_) {
+                int cells, rows;
+                hm::tile_limits(b.prob, &cells, &rows);
+                b.tile_x = tx_;
+                b.tile_y = std::min(ty_, std::min(rows, cells / tx_));
+            }
+            whole += whole_lines(b) ? b.prob.N : -b.prob.N;
+        }
+        return whole >= 0;
     }
 
     // Whole 128-byte lines in every row of the domain's tiles.  A launch has one
@@ -130,21 +145,13 @@ class BatchRunner {
         // domains alone would leave most of the GPU idle, and the halo
         // re-reads cost little there)
         balanced_.assign(d, d + n);
+        const bool nt = fit_tiles();
         int64_t cols = 0, tiles16 = 0;
-        int64_t whole = 0;  // cells in whole lines, less the others
-        for (hm::BatchDomain& b : balanced_) {
-            if (!own_tiles_) {
-                int cells, rows;
-                hm::tile_limits(b.prob, &cells, &rows);
-                b.tile_x = tx_;
-                b.tile_y = std::min(ty_, std::min(rows, cells / tx_));
-            }
-            whole += whole_lines(b) ? b.prob.N : -b.prob.N;
+        for (const hm::BatchDomain& b : balanced_) {
             const int64_t c = columns(b);
             cols += c;
             tiles16 += c * ((b.prob.nz + 15) / 16);
         }
-        const bool nt = whole >= 0;
         const int64_t min_chunk = tiles16 >= 2 * static_cast<int64_t>(cus_) ? 16 : 4;
         auto chunk_of = [&](const hm::BatchDomain& b, int64_t per_cols) {
             const int64_t chunks = std::max<int64_t>(per_cols, (b.prob.nz + maxc_ - 1) / maxc_);
@@ -168,8 +175,7 @@ class BatchRunner {
         HIP_TRY(hipMemcpyAsync(dev_[j], host_[j], bytes_, hipMemcpyHostToDevice, stream_));
         HIP_TRY(hipEventRecord(copied_[j], stream_));
         HIP_TRY(hipEventRecord(t0_, stream_));
-        if (k == kmax_ && graphs_ok_ && !exec_[nt ? 1 : 0][0]) capture(nt);
-        if (k == kmax_ && graphs_ok_) {
+        if (k == kmax_ && exec_[nt ? 1 : 0][j]) {
             HIP_TRY(hipGraphLaunch(exec_[nt ? 1 : 0][j], stream_));
         } else {
             for (int kk = 0; kk < k; ++kk)
@@ -189,8 +195,6 @@ class BatchRunner {
     }
 
     int kmax() const { return kmax_; }
-    int tile_x() const { return tx_; }
-    int tile_y() const { return ty_; }
 
     void release()
     {
@@ -295,7 +299,6 @@ class BatchRunner {
     hipEvent_t copied_[2] = {nullptr, nullptr};
     hipGraphExec_t exec_[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};  // [store policy][table copy]
     bool own_tiles_ = false;
-    bool graphs_ok_ = false;
     int slot_ = 0;
     hipEvent_t t0_ = nullptr, t1_ = nullptr;
     int last_k_ = 0;
@@ -362,11 +365,9 @@ int lbm_group_create(lbm_ctx* const* ctxs, int32_t n, lbm_group** out)
     g->ctx.assign(ctxs, ctxs + n);
     const lbm_params& p = ctxs[0]->prm;
     const int tx = hm_rt::env_int("LBM_BATCH_TILE_X", 0), ty = hm_rt::env_int("LBM_BATCH_TILE_Y", 0);
-    int64_t whole = 0;
-    for (const lbm_ctx* c : g->ctx) whole += BatchRunner::whole_lines(domain_of(c, 0)) ? c->prob.N : -c->prob.N;
-    const bool nt = whole >= 0;
-    const int rc = g->runner.init(p.storage, p.ncomp, p.c_ns, tx, ty, n, hm_rt::env_int("LBM_GRAPH_STEPS", 16), nt,
-                                  ctxs[0]->stream);
+    for (const lbm_ctx* c : g->ctx) g->doms.push_back(domain_of(c, 0));
+    const int rc = g->runner.init(p.storage, p.ncomp, p.c_ns, tx, ty, n, hm_rt::env_int("LBM_GRAPH_STEPS", 16),
+                                  g->doms, ctxs[0]->stream);
     if (rc) {
         delete g;
         return rc;
@@ -1006,7 +1007,7 @@ int lbm_server_create(const lbm_server_cfg* cfg, void* reserved, lbm_server** ou
     s->budget = cfg->hbm_budget_bytes ? cfg->hbm_budget_bytes : static_cast<uint64_t>(0.9 * free_b);
     s->pool.init(s->budget, uint64_t(8) << 30);
     const int rc = s->runner.init(cfg->storage, cfg->ncomp, cfg->c_ns, tx, ty, cfg->max_slots, cfg->steps_per_tick,
-                                  false, s->stream);
+                                  {}, s->stream);
     if (rc) return fail(rc);
     s->worker = std::thread([s] { s->run(); });
     *out = s;

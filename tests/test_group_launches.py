@@ -34,3 +34,43 @@ def test_an_asked_tile_is_used(driver, storage, ncomp, asked, got):
     if asked[1]:
         env["LBM_BATCH_TILE_Y"] = asked[1]
     assert _tiles(_group(driver, storage, ncomp, 20, (40, 40, 40), (131, 50, 20), **env)) == {got}
+
+
+def _after_creation(lines):
+    return lines[lines.index("created") + 1:]
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16s"])
+def test_server_captures_its_graphs_when_it_is_created(driver, storage):
+    """Requests of whole lines and of ragged rows, so of both store policies:
+    every full tick replays a graph, none is captured on the way."""
+    out = _server(driver, storage, 2, (0, 0), (64, 64, 16), (33, 17, 40), (128, 16, 16), (70, 45, 9))
+    ticks = _after_creation(out)
+    assert not [x for x in ticks if x.startswith(("capture", "launch"))]
+    policies = {x.split()[1] for x in ticks if x.startswith("graph")}
+    assert policies == ({"1"} if storage == "f64" else {"0", "1"})
+    assert {x.split()[2] for x in out if x.startswith("capture")} == policies
+
+
+@pytest.mark.parametrize("env", [{}, {"LBM_BATCH_TILE_X": 32}, {"LBM_BATCH_TILE_X": 64}], ids=str)
+def test_group_captures_the_policy_that_it_launches(driver, env):
+    # one component in FP16: rows of 64 cells are whole lines, of 32 are not
+    out = _group(driver, "f16s", 1, 36, (64, 48, 20), (128, 32, 20), **env)
+    steps = _after_creation(out)
+    assert not [x for x in steps if x.startswith("capture")]
+    policy = {x.split()[2] for x in out if x.startswith("capture")}
+    assert len(policy) == 1
+    assert [x for x in steps if not x.startswith(("tile", "time"))] == (
+        2 * ["graph " + min(policy)] + 4 * ["launch " + min(policy)])
+
+
+@pytest.mark.parametrize("failing", [1, 2, 3, 4])
+def test_a_failed_capture_leaves_the_other_graphs(driver, failing):
+    out = _plan.run_driver(driver, ["server", lbm.STORAGE["f16s"], 2, 1, 0, 0, *(64, 64, 16, 33, 17, 40) * 3],
+                           env=dict(FAKE_FAIL_CAPTURE=failing))
+    ticks = _after_creation(out)
+    assert sum(x.startswith("capture") for x in out) == 3
+    graphs, launches = (sum(x.startswith(k) for x in ticks) for k in ("graph", "launch"))
+    # twelve ticks of four steps, alternately from two tables, six of each policy:
+    # three of them lost their graph
+    assert (graphs, launches) == (9, 3 * 4)
