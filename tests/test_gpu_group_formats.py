@@ -1,0 +1,74 @@
+"""Groups of every batched instance with tiles fitted to ragged domains, tiles
+that are asked for, and a server that goes from one store policy to the other:
+bitwise each domain stepped alone."""
+import numpy as np
+import pytest
+
+from paper_2206_11524_amd import inputs, lbm
+
+pytestmark = pytest.mark.gpu
+
+RAGGED, WHOLE = [(33, 17, 9), (67, 40, 21), (130, 9, 11)], [(64, 16, 20), (128, 24, 9)]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    yield
+
+
+def _workload(shape, ncomp, c_ns):
+    w = inputs.random_state(shape, 990, ncomp=ncomp, c_ns=c_ns, ns_choices=[0.0, 0.4, 1.0], rho_range=(0.3, 0.7))
+    w.G, w.G_ads, w.F_ext = (0.7 if ncomp == 2 else 0.0), (0.2, -0.15), (2e-4, -1e-4, 3e-4)
+    w.reservoirs = [(0, 0, 2, (0.6, 0.4)), (2, shape[2] - 1, shape[2], (0.4, 0.6))]
+    return w
+
+
+def _alone(w, storage, steps):
+    sim = lbm.from_workload(w, storage=storage)
+    sim.step(steps)
+    f = sim.populations()
+    sim.close()
+    return f
+
+
+@pytest.mark.parametrize("tile", [None, (64, 8), (32, 8)], ids=str)
+@pytest.mark.parametrize("storage,ncomp,c_ns", [("f64", 1, 1), ("f64", 2, 2), ("f64", 2, 1), ("f32", 1, 1), ("f32", 2, 2),
+                                                ("f16s", 1, 1), ("f16s", 2, 2), ("bf16s", 1, 1), ("bf16s", 2, 2)])
+def test_group_equals_each_domain_alone(monkeypatch, storage, ncomp, c_ns, tile):
+    import torch
+    if tile == (32, 8) and ncomp == 2 and storage != "f64":
+        tile = (64, 8)  # the only one of the pair layout
+    for k, v in zip(("LBM_BATCH_TILE_X", "LBM_BATCH_TILE_Y"), tile or ()):
+        monkeypatch.setenv(k, str(v))
+    steps = 19  # a graph replay and single launches
+    for shapes in (RAGGED, WHOLE):
+        ws = [_workload(s, ncomp, c_ns) for s in shapes]
+        ref = [_alone(w, storage, steps) for w in ws]
+        with torch.cuda.stream(torch.cuda.Stream()):
+            sims = [lbm.from_workload(w, storage=storage) for w in ws]
+            g = lbm.Group(sims)
+            g.step(steps)
+            for s, f in zip(sims, ref):
+                assert np.isfinite(f).all() and np.array_equal(s.populations(), f)
+            g.close()
+            for s in sims:
+                s.close()
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16s"])
+def test_server_from_one_store_policy_to_the_other(storage):
+    """Whole lines, ragged rows, whole lines again, each alone in the server."""
+    srv = lbm.Server(storage=storage, max_slots=2, steps_per_tick=8, max_cells=67 * 40 * 21)
+    for shape in (WHOLE[0], RAGGED[1], RAGGED[0], WHOLE[1]):
+        w = _workload(shape, 2, 1)
+        r = srv.wait(srv.submit_workload(w, 21, want_rho=True), 60.0)
+        sim = lbm.from_workload(w, storage=storage)
+        sim.step(21)
+        m = sim.moments()
+        sim.close()
+        assert r["status"] == 0 and r["steps_done"] == 21
+        assert np.array_equal(r["rho"], m["rho"]) and r["mass"][:2] == list(m["mass"])
+    srv.close()
