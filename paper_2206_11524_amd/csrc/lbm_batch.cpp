@@ -109,17 +109,38 @@ class BatchRunner {
     // policy.
     bool fit_tiles()
     {
+        if (own_tiles_) spread_tiles();
+        else
+            for (hm::BatchDomain& b : balanced_) set_tile(b, tx_, ty_);
         int64_t whole = 0;  // cells in whole lines, less the others
-        for (hm::BatchDomain& b : balanced_) {
-            if (!own_tiles_) {
-                int cells, rows;
-                hm::tile_limits(b.prob, &cells, &rows);
-                b.tile_x = tx_;
-                b.tile_y = std::min(ty_, std::min(rows, cells / tx_));
-            }
-            whole += whole_lines(b) ? b.prob.N : -b.prob.N;
-        }
+        for (const hm::BatchDomain& b : balanced_) whole += whole_lines(b) ? b.prob.N : -b.prob.N;
         return whole >= 0;
+    }
+
+    // Fitted tiles are few in small domains, and a plane of one waits as long as a
+    // plane of a smaller one: where even chunks of four planes leave blocks without
+    // a tile, the domains take 64-wide tiles, if no block and no CU gets a second
+    // tile for it (the tiles go to the first blocks of the order of k_step_batch, so to
+    // as few XCDs as hold them).  us a step, fitted / 64-wide: eight 32^3 domains in
+    // FP32 35 / 31, with one component 26 / 22, sixteen 24^3 in FP16 with one component
+    // 25 / 23; but five 16^3 in FP32 with one component, 20 tiles on one CU each or 40
+    // on as many CUs, 14 / 20.
+    void spread_tiles()
+    {
+        int64_t fitted = 0, wide = 0;
+        for (const hm::BatchDomain& b : balanced_) {
+            hm::BatchDomain w = b;
+            set_tile(w, 64, 8);
+            const int64_t chunks = (b.prob.nz + 3) / 4;
+            fitted += columns(b) * chunks;
+            wide += columns(w) * chunks;
+        }
+        auto per_cu = [&](int64_t tiles) {
+            const int64_t xcd_cus = std::max(1, cus_ / 8);
+            return (std::min<int64_t>(tiles, grid_ / 8) + xcd_cus - 1) / xcd_cus;
+        };
+        if (fitted < wide && wide <= grid_ && per_cu(wide) <= per_cu(fitted))
+            for (hm::BatchDomain& b : balanced_) set_tile(b, 64, 8);
     }
 
     // Whole 128-byte lines in every row of the domain's tiles.  A launch has one
@@ -217,6 +238,15 @@ class BatchRunner {
     }
 
   private:
+    // Tile of w x h cells, of as many of the rows as the format's tiles hold.
+    static void set_tile(hm::BatchDomain& b, int w, int h)
+    {
+        int cells, rows;
+        hm::tile_limits(b.prob, &cells, &rows);
+        b.tile_x = w;
+        b.tile_y = std::min(h, std::min(rows, cells / w));
+    }
+
     static int64_t columns(const hm::BatchDomain& b)
     {
         return static_cast<int64_t>((b.prob.nx + b.tile_x - 1) / b.tile_x) *
@@ -240,6 +270,8 @@ class BatchRunner {
             shapes_now_.push_back(b.prob.nx);
             shapes_now_.push_back(b.prob.ny);
             shapes_now_.push_back(b.prob.nz);
+            shapes_now_.push_back(b.tile_x);
+            shapes_now_.push_back(b.tile_y);
         }
         shapes_now_.push_back(static_cast<int>(min_chunk));
         if (shapes_now_ == shapes_planned_) return planned_;

@@ -128,7 +128,7 @@ hipError_t launch_diagnostics(const Problem&, const void*, const float*, bool, d
     for (int k = 0; k < 5; ++k) out[k] = 0.0;
     return hipSuccess;
 }
-int batch_blocks_per_cu(int, int, int) { return 1; }
+int batch_blocks_per_cu(int storage, int ncomp, int) { return ncomp == 1 && storage != kF64 ? 2 : 1; }
 int batch_encode(int, const BatchDomain* d, int n, void*)
 {
     Lock l;

@@ -74,3 +74,17 @@ def test_a_failed_capture_leaves_the_other_graphs(driver, failing):
     # twelve ticks of four steps, alternately from two tables, six of each policy:
     # three of them lost their graph
     assert (graphs, launches) == (9, 3 * 4)
+
+
+# us a step, fitted / 64-wide tiles
+@pytest.mark.parametrize("storage,ncomp,edge,n,got", [
+    ("f32", 2, 32, 8, (64, 8)),    # 35 / 31
+    ("f32", 1, 32, 8, (64, 8)),    # 26 / 22
+    ("f16s", 1, 24, 16, (64, 8)),  # 25 / 23
+    ("f32", 2, 24, 16, (24, 12)),  # 31 / 34: some blocks would get a second tile
+    ("f32", 1, 16, 5, (16, 16)),   # 14 / 20: some CUs would
+    ("f32", 2, 40, 12, (40, 10)),  # enough tiles
+    ("f16s", 2, 128, 8, (64, 8)),
+])
+def test_small_batches_spread_over_the_device(driver, storage, ncomp, edge, n, got):
+    assert _tiles(_group(driver, storage, ncomp, 16, *[(edge, edge, edge)] * n)) == {got}
