@@ -61,8 +61,8 @@ def test_group_equals_each_domain_alone(monkeypatch, storage, ncomp, c_ns, tile)
 @pytest.mark.parametrize("storage", ["f64", "f32", "f16s"])
 def test_server_from_one_store_policy_to_the_other(storage):
     """Whole lines, ragged rows, whole lines again, each alone in the server."""
-    srv = lbm.Server(storage=storage, max_slots=2, steps_per_tick=8, max_cells=67 * 40 * 21)
-    for shape in (WHOLE[0], RAGGED[1], RAGGED[0], WHOLE[1]):
+    srv = lbm.Server(storage=storage, max_slots=2, steps_per_tick=8, max_cells=70 * 69 * 65)
+    for shape in (WHOLE[0], (67, 66, 67), RAGGED[0], (70, 69, 65)):  # the large ones are stored through the caches
         w = _workload(shape, 2, 1)
         r = srv.wait(srv.submit_workload(w, 21, want_rho=True), 60.0)
         sim = lbm.from_workload(w, storage=storage)

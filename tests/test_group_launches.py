@@ -44,7 +44,7 @@ def _after_creation(lines):
 def test_server_captures_its_graphs_when_it_is_created(driver, storage):
     """Requests of whole lines and of ragged rows, so of both store policies:
     every full tick replays a graph, none is captured on the way."""
-    out = _server(driver, storage, 2, (0, 0), (64, 64, 16), (33, 17, 40), (128, 16, 16), (70, 45, 9))
+    out = _server(driver, storage, 2, (0, 0), (64, 64, 16), (67, 67, 67), (128, 16, 16), (70, 69, 65))
     ticks = _after_creation(out)
     assert not [x for x in ticks if x.startswith(("capture", "launch"))]
     policies = {x.split()[1] for x in ticks if x.startswith("graph")}
@@ -55,7 +55,7 @@ def test_server_captures_its_graphs_when_it_is_created(driver, storage):
 @pytest.mark.parametrize("env", [{}, {"LBM_BATCH_TILE_X": 32}, {"LBM_BATCH_TILE_X": 64}], ids=str)
 def test_group_captures_the_policy_that_it_launches(driver, env):
     # one component in FP16: rows of 64 cells are whole lines, of 32 are not
-    out = _group(driver, "f16s", 1, 36, (64, 48, 20), (128, 32, 20), **env)
+    out = _group(driver, "f16s", 1, 36, (64, 48, 200), (128, 32, 20), **env)
     steps = _after_creation(out)
     assert not [x for x in steps if x.startswith("capture")]
     policy = {x.split()[2] for x in out if x.startswith("capture")}
@@ -66,7 +66,7 @@ def test_group_captures_the_policy_that_it_launches(driver, env):
 
 @pytest.mark.parametrize("failing", [1, 2, 3, 4])
 def test_a_failed_capture_leaves_the_other_graphs(driver, failing):
-    out = _plan.run_driver(driver, ["server", lbm.STORAGE["f16s"], 2, 1, 0, 0, *(64, 64, 16, 33, 17, 40) * 3],
+    out = _plan.run_driver(driver, ["server", lbm.STORAGE["f16s"], 2, 1, 0, 0, *(64, 64, 16, 67, 67, 67) * 3],
                            env=dict(FAKE_FAIL_CAPTURE=failing))
     ticks = _after_creation(out)
     assert sum(x.startswith("capture") for x in out) == 3
@@ -88,3 +88,16 @@ def test_a_failed_capture_leaves_the_other_graphs(driver, failing):
 ])
 def test_small_batches_spread_over_the_device(driver, storage, ncomp, edge, n, got):
     assert _tiles(_group(driver, storage, ncomp, 16, *[(edge, edge, edge)] * n)) == {got}
+
+
+# us a step, non-temporal / cached stores
+@pytest.mark.parametrize("storage,ncomp,shape,n,policy", [
+    ("f32", 2, (300, 50, 1), 4, "1"),   # 9 MB: 15.0 / 16.6
+    ("f16s", 2, (28, 28, 28), 8, "1"),  # 13 MB: 24.3 / 25.9
+    ("f32", 2, (33, 33, 33), 6, "0"),   # 33 MB: 34.7 / 30.8
+    ("f32", 1, (62, 61, 60), 3, "0"),
+    ("f32", 2, (64, 64, 64), 4, "1"),   # whole lines
+])
+def test_small_batches_store_past_the_caches(driver, storage, ncomp, shape, n, policy):
+    out = _group(driver, storage, ncomp, 20, *[shape] * n)
+    assert {x.split()[-1] for x in out if x.startswith(("capture", "graph", "launch"))} == {policy}
