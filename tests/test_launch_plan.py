@@ -2,6 +2,7 @@
 and chunk may be, from times measured on an MI355X."""
 import pytest
 
+import _box_cases
 import _plan
 
 
@@ -88,3 +89,14 @@ def test_sweep_tile_settings_stay_out_of_groups_and_servers(planner, tile):
     for d, p, q in zip(domains, _plan.plans(planner, domains), _plan.plans(planner, domains, env=tile)):
         assert (p.group, p.server) == (q.group, q.server), d
         assert q.tile[0] == tile.get("LBM_TILE_X", 64) and q.box is None
+
+
+@pytest.mark.parametrize("fmt", _box_cases.CASES, ids=lambda f: "-".join(map(str, f)))
+def test_box_cases_take_the_box_kernel(planner, fmt):
+    shapes, boxes = _box_cases.CASES[fmt]
+    assert all(p.box for p in _plan.plans(planner, [(s, *fmt) for s in shapes]))
+    for box in boxes:
+        p = _plan.plans(planner, [(_box_cases.BOXED, *fmt)], env=dict(LBM_BOX="%d,%d,%d" % box))[0]
+        assert p.box == box
+    for env in (dict(LBM_BOX="0"), dict(LBM_TILE_X=64), dict(LBM_BOX="64,64,64")):  # the last fits no format
+        assert not any(p.box for p in _plan.plans(planner, [(s, *fmt) for s in shapes], env=env))
