@@ -2,7 +2,7 @@
 //
 // The 2.5-D sweeps of lbm_kernels.hip march a block along z, one memory round
 // trip per plane; on a domain whose planes give only a few blocks that chain of
-// round trips is the whole step (32^3 in FP64: six planes, 26.3 us a step).  Here a
+// round trips is the whole step (32^3 in FP64: six planes, 25.7 us a step).  Here a
 // block owns a box of bx x by x bz cells and takes it in ONE round trip: waves
 // of their own pull the cells of the box and of the one-cell halo around it at
 // once (the halo only for the densities and n_s), exchange densities through
@@ -10,8 +10,8 @@
 // re-reads one to two times the box, from the caches that a small domain's state
 // sits in; what bounds the step then is one launch, one round trip and, from
 // about 10^5 cells, the caches' bandwidth.  Us a step, sweep / box: 500 x 2 x 1
-// FP64 7.6 / 5.6, 300 x 50 x 1 FP32 7.4 / 5.4, 32^3 FP64 26.3 / 8.4, 48 x 48 x 64
-// FP16 20.7 / 11.6, 64 x 64 x 128 FP32 with one component 18.1 / 15.1.
+// FP64 7.1 / 5.0, 300 x 50 x 1 FP32 7.0 / 4.7, 32^3 FP64 25.7 / 8.1, 48 x 48 x 64
+// FP16 21.7 / 11.1, 64 x 64 x 128 FP32 with one component 18.5 / 15.9.
 #include "lbm_device.h"
 
 #include <algorithm>
@@ -242,16 +242,21 @@ bool box_fits(const Problem& p, int bx, int by, int bz)
     return waves * 64 <= kBoxMaxThreads && bytes < (int64_t(1) << 31);
 }
 
-// The box kernel takes a domain up to this many cells; beyond it the sweep,
-// which re-reads a ring per plane instead of a whole halo, moves less from the
-// caches.  Microseconds a step, box / sweep: two components in 16 bits 18.8 /
-// 21.7 at 64^3 but 55 / 46 at 96^3; in FP32 23.9 / 25.5 at 57^3, 13.3 / 23.3 at 32 x
-// 32 x 128, but 26.5 / 26.8 at 64^3 and 82 / 70 at 96^3; in FP64, and in FP32 with
-// the GS-WBS (a thread per component), 8.4 / 26.1 at 32^3, 27.2 / 29.8 at
-// 47 x 47 x 43 but 36.6 / 31.6 at 50^3; one component, which pulls no halo,
-// 15.1 / 18.1 (FP32) at 64 x 64 x 128, 15.9 / 20.1 (FP16) and 32.6 / 40.5 (FP64)
-// at 80^3.  One plane deep 10.2 / 13.3 (FP32) and 20.6 / 24.5 (FP64) at 360 x 360,
-// but 20.2 / 19.0 (FP32) at 500 x 500.
+// The box kernel takes a domain up to this many cells; beyond, the sweep, which
+// re-reads a ring per plane instead of a whole halo, comes to move less from the
+// caches.  The bounds are below the sizes where the two meet: they were set while
+// the box stored past the caches at every size (it then lost at 64^3 in FP32 and 50^3
+// in FP64), and small domains gain most.  us a step, box / sweep, at the bound and
+// beyond: two components in 16 bits 16.4 / 21.9 at 64^3, 29 / 30 at 80^3, 47 / 43 at 96^3;
+// in FP32 18.6 / 23.1 at 57^3, 23.3 / 25.9 at 64^3, 32 / 31 at 72^3; in FP64 (a thread per
+// component) 23.6 / 29.5 at 47 x 47 x 43, 28.8 / 30.2 at 50^3, 37 / 32 at 56^3, and in FP32
+// with the GS-WBS 17.1 / 27.5 at 45^3, 22.1 / 27.8 at 56^3.  One component pulls no halo
+// and meets the sweep at twice the bound, sooner or later with the shape: in FP32
+// 15.9 / 18.5 at 64 x 64 x 128, 29.1 / 34.0 at 128 x 64 x 128, but 28.4 / 26.8 at 96^3 and
+// 33.4 / 31.1 at 100^3; in FP16 13.9 / 16.1, 24.3 / 26.0, 25.6 / 25.1 and 27.1 / 28.0; in
+// FP64 30.4 / 37.9 at 80^3, 62.8 / 70.1 at 128 x 64 x 128, 56.7 / 57.1 at 96^3.  One plane
+// deep 9.2 / 13.7 (FP32) and 18.2 / 25.3 (FP64) at 360 x 360, 15.5 / 18.5 (FP32) at 500 x
+// 500.
 static int64_t box_max_cells(const Problem& p)
 {
     if (p.nz == 1) return int64_t(1) << 17;

@@ -387,26 +387,6 @@ __device__ __forceinline__ bool reservoir_dr(const Args<T>& a, int s, int x, int
     return in;
 }
 
-// Both components at once (pair kernel).
-template <typename T>
-__device__ __forceinline__ bool reservoir_dr2(const Args<T>& a, int x, int y, int z, T& dr0, T& dr1)
-{
-    bool in = false;
-    dr0 = T(0);
-    dr1 = T(0);
-#pragma unroll
-    for (int r = 0; r < kMaxRes; ++r) {
-        if (r < a.n_res) {
-            const int c = a.res_axis[r] == 0 ? x : (a.res_axis[r] == 1 ? y : z);
-            const bool hit = !in && c >= a.res_lo[r] && c < a.res_hi[r];
-            dr0 = hit ? a.res_dr[r][0] : dr0;
-            dr1 = hit ? a.res_dr[r][1] : dr1;
-            in = in || hit;
-        }
-    }
-    return in;
-}
-
 // Reservoir membership as bit masks (pair kernel): bit r is set when the cell
 // lies in slot r.  Slots along x or y depend on the cell's column only, so a
 // thread computes their bits once; slots along z depend on the plane only, the

@@ -752,7 +752,7 @@ __global__ __launch_bounds__((kThreads<ST, NC, FS, CELLS>)) void k_step(Args<typ
 {
     // One block fits a CU, two with one component in FP32 arithmetic (77 KB of
     // LDS) and, but for two n_s fields with the GS-WBS, with the smaller blocks of
-    // thin domains: a round is 256 or 512 blocks.  Runs per round instead of one run of the whole grid: 181^3 in FP64,
+    // thin domains: a round of the 256 CUs is 256 or 512 blocks.  Runs per round instead of one run of the whole grid: 181^3 in FP64,
     // 690 blocks, 948 us against 1050.
     constexpr bool TWO = CELLS < kBlockCells<ST, NC, FS> || (NC == 1 && sizeof(typename ST::T) == 4);
     const int L = xcd_tile(blockIdx.x, gridDim.x, TWO ? 512 : 256);

@@ -125,12 +125,14 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     // One block fits a CU (registers and LDS), so blocks run in rounds of one
     // per CU, and a block takes about (chunk + 8) plane times: the halo planes,
     // the pipeline fill and drain and the block's start cost as much as about
-    // eight planes (fitted to timings of 192^3 to 384^3 domains).  Take the
-    // tile and chunking with the least rounds x (chunk + 8) x plane time, the
-    // fewest chunks among equals.  Chunks shorter than 16 planes spend too much
-    // on their halo, unless the domain would then give fewer than two such
-    // tiles per CU: a small domain would leave most CUs idle, and its halo
-    // re-reads are L2 hits.
+    // eight planes (fitted to timings of 192^3 to 384^3 domains).  Take the tile and
+    // chunking with the least rounds x (chunk + 8) x plane time, the fewest chunks
+    // among equals.  Two blocks fit a CU with one component in FP32 arithmetic and in
+    // thin domains, but share its time: over 123 domains with one component the
+    // choices are 1.8 % off the best with one block counted per CU, 10 % with two.
+    // Chunks shorter than 16 planes spend too much on their halo, unless the domain
+    // would then give fewer than two such tiles per CU: a small domain would leave
+    // most CUs idle, and its halo re-reads are L2 hits.
     //
     // The sweeps take any tile within tile_limits.  A plane time falls with the
     // lanes that have a cell, by 30 % at most where the domain streams from
@@ -148,10 +150,10 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     // domains of 1.4 thousand to 14 million cells in six formats, up to 16 tiles and
     // chunks each, the choice is 1.2 % off the best on average.
     // Even parts of the domain are tried beside 64 x 8: 131^3 in FP16 takes 44 x 11
-    // tiles (108 us a step, 136 with 64 x 8), 100^3 50 x 9 (48 / 65), 72^3 in FP32
-    // 36 x 11 (29 / 42); 192^3 and 224^3 keep 64 x 8 (271 against 277 us with 64 x 7,
-    // 429 against 516 with 56 x 9 in FP16); one component 150^3 50 x 10 (FP32 115 /
-    // 167, FP16 76 / 104); the GS-WBS in FP32 150 x 150 x 100 50 x 10 (203 / 258).
+    // tiles (109 us a step, 125 with 64 x 8), 100^3 50 x 10 (48 / 56); 192^3 and 224^3
+    // keep 64 x 8 (264 against 266 us with 64 x 7, 416 against 516 with 56 x 9 in FP16);
+    // one component 150^3 50 x 9 (FP32 115 / 148, FP16 80 / 91); the GS-WBS in FP32 150 x
+    // 150 x 100 50 x 9 (205 / 236).
     //
     // In a batched launch every block strides over many tiles: there the tile of
     // the least columns x plane time is taken, with 60 % of the time following
@@ -239,8 +241,8 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     // Non-temporal stores keep the written state out of the caches' way, but
     // where a tile's rows start or end inside a 128-byte line the two tiles that
     // share it each write part of it, and only a cached line is merged before it
-    // goes out: 131^3 in FP32 169 us a step with cached stores against 205, 100^3 in
-    // FP16 48 against 56; with whole lines non-temporal stores are the faster ones
+    // goes out: 131^3 in FP32 179 us a step with cached stores against 206, 100^3 in
+    // FP16 49 against 56; with whole lines non-temporal stores are the faster ones
     // (256^3 in FP32 970 against 997).
     // FP64 keeps them (150^3 548 against 577, 160^3 528 against 550).
     if (l.bx > 0) l.nt_stores = hm::box_nt_stores(p);
