@@ -11,7 +11,7 @@
 // sits in; what bounds the step then is one launch, one round trip and, from
 // about 10^5 cells, the caches' bandwidth.  Us a step, sweep / box: 500 x 2 x 1
 // FP64 7.1 / 5.0, 300 x 50 x 1 FP32 7.0 / 4.7, 32^3 FP64 25.7 / 8.1, 48 x 48 x 64
-// FP16 21.7 / 11.1, 64 x 64 x 128 FP32 with one component 18.5 / 15.9.
+// FP16 21.7 / 11.1, 64 x 64 x 128 FP32 with one component 18.5 / 15.7.
 #include "lbm_device.h"
 
 #include <algorithm>
@@ -252,7 +252,7 @@ bool box_fits(const Problem& p, int bx, int by, int bz)
 // component) 23.6 / 29.5 at 47 x 47 x 43, 28.8 / 30.2 at 50^3, 37 / 32 at 56^3, and in FP32
 // with the GS-WBS 17.1 / 27.5 at 45^3, 22.1 / 27.8 at 56^3.  One component pulls no halo
 // and meets the sweep at twice the bound, sooner or later with the shape: in FP32
-// 15.9 / 18.5 at 64 x 64 x 128, 29.1 / 34.0 at 128 x 64 x 128, but 28.4 / 26.8 at 96^3 and
+// 15.7 / 18.5 at 64 x 64 x 128, 29.1 / 34.0 at 128 x 64 x 128, but 28.4 / 26.8 at 96^3 and
 // 33.4 / 31.1 at 100^3; in FP16 13.9 / 16.1, 24.3 / 26.0, 25.6 / 25.1 and 27.1 / 28.0; in
 // FP64 30.4 / 37.9 at 80^3, 62.8 / 70.1 at 128 x 64 x 128, 56.7 / 57.1 at 96^3.  One plane
 // deep 9.2 / 13.7 (FP32) and 18.2 / 25.3 (FP64) at 360 x 360, 15.5 / 18.5 (FP32) at 500 x
@@ -302,17 +302,20 @@ bool choose_box(const Problem& p, int cus, int* bx, int* by, int* bz)
 
 // While both buffers stay in the L2 caches (4 MB in each of 8 XCDs), stores past
 // them cost nothing or save up to a tenth: the lines that they would fill are
-// those that the next step reads.  Beyond, the rows of a box start and end inside
-// lines, which two boxes write in parts, and cached stores merge them.  Cached
+// those that the next step reads.  Beyond, the rows of most boxes start and end
+// inside lines, which two boxes write in parts, and cached stores merge them; rows of
+// whole lines keep non-temporal ones (64 x 64 x 128 with one component in FP32 15.9
+// cached, 15.7 past the caches).  Cached
 // against non-temporal, us a step: 41^3 in FP32 (10 MB a buffer) 9.3 / 8.7, 57^3 in
 // FP16 (14 MB) 15.2 / 17.3, 53 x 148 x 28 in FP16 (17 MB) 16.5 / 20.4, 42^3 in FP64
 // (23 MB) 17.9 / 20.6; one component crosses later: 247 x 111 x 8 in FP32 (17 MB)
 // 11.6 / 10.1, 101 x 118 x 21 (19 MB) 11.2 / 11.1, 268 x 22 x 51 (23 MB) 12.0 / 13.3,
 // 261 x 95 x 19 (36 MB) 17.1 / 22.5, in FP64 (72 MB) 31.9 / 38.4.
-bool box_nt_stores(const Problem& p)
+bool box_nt_stores(const Problem& p, int bx)
 {
     const int64_t state = p.N * kQ * storage_bytes(p.storage) * p.ncomp;
-    return state < (p.ncomp == 2 ? 14000000 : 22000000);
+    const int word = storage_bytes(p.storage) * (pair_layout(p.storage, p.ncomp, p.forcing) ? 2 : 1);
+    return state < (p.ncomp == 2 ? 14000000 : 22000000) || (p.nx * word % 128 == 0 && bx * word % 128 == 0);
 }
 
 template <typename ST, int NC, int CNS, int FS>

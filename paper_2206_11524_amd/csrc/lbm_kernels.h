@@ -76,7 +76,7 @@ bool box_fits(const Problem& p, int bx, int by, int bz);
 bool choose_box(const Problem& p, int cus, int* bx, int* by, int* bz);
 
 // Store policy of the box kernel: non-temporal stores, or cached ones.
-bool box_nt_stores(const Problem& p);
+bool box_nt_stores(const Problem& p, int bx);
 
 hipError_t launch_step_box(const Problem& p, const Launch& l, int64_t t, const void* A, void* B,
                            const float* ns, hipStream_t s);

@@ -245,7 +245,7 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     // FP16 49 against 56; with whole lines non-temporal stores are the faster ones
     // (256^3 in FP32 970 against 997).
     // FP64 keeps them (150^3 548 against 577, 160^3 528 against 550).
-    if (l.bx > 0) l.nt_stores = hm::box_nt_stores(p);
+    if (l.bx > 0) l.nt_stores = hm::box_nt_stores(p, l.bx);
     else l.nt_stores = p.storage == hm::kF64 || (l.tile_x * word % 128 == 0 && p.nx * word % 128 == 0);
     return l;
 }

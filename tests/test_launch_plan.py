@@ -100,3 +100,11 @@ def test_box_cases_take_the_box_kernel(planner, fmt):
         assert p.box == box
     for env in (dict(LBM_BOX="0"), dict(LBM_TILE_X=64), dict(LBM_BOX="64,64,64")):  # the last fits no format
         assert not any(p.box for p in _plan.plans(planner, [(s, *fmt) for s in shapes], env=env))
+
+
+def test_box_rows_of_whole_lines_are_stored_past_the_caches(planner):
+    """Beyond the L2 as well: 64 x 64 x 128 with one component in FP32 15.7 us a
+    step, 15.9 with cached stores."""
+    for shape, nt in (((64, 64, 128), True), ((66, 62, 128), False)):
+        p = _plan.plans(planner, [(shape, "f32", 1, 1, "shan-chen")])[0]
+        assert p.box and p.nt is nt
