@@ -1337,8 +1337,8 @@ static hipError_t step_t(const Problem& p, const Launch& l, int64_t t, const voi
     a.nzc = (p.nz + l.zchunk - 1) / l.zchunk;
     a.t = static_cast<uint32_t>(t);
     const int nblocks = a.ntx * a.nty * a.nzc;
-    // one instance per block size and store policy (FP64 and one plane keep
-    // non-temporal stores), and of the pair kernel per rounding mode; the split
+    // one instance per block size and store policy (two components in FP64 and one
+    // plane keep non-temporal stores), and of the pair kernel per rounding mode; the split
     // kernels branch on it (their two store sequences are alike)
     constexpr int CELLS = kBlockCells<ST, NC, FS>;
     auto go = [&](auto rnd, auto aux, auto cells) {
@@ -1348,7 +1348,7 @@ static hipError_t step_t(const Problem& p, const Launch& l, int64_t t, const voi
                            static_cast<E*>(B), ns);
     };
     using Nt = std::integral_constant<int, kNT>;
-    using Cached = std::integral_constant<int, ONE || sizeof(E) == 8 ? kNT : 0>;
+    using Cached = std::integral_constant<int, ONE || (sizeof(E) == 8 && NC == 2) ? kNT : 0>;
     using Full = std::integral_constant<int, CELLS>;
     using Thin = std::integral_constant<int, std::min(CELLS, kThinCells)>;
     auto block = [&](auto rnd, auto aux) { l.cells < CELLS ? go(rnd, aux, Thin{}) : go(rnd, aux, Full{}); };

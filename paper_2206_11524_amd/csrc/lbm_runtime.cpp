@@ -142,13 +142,13 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     // with 63 x 2 and 8 planes 54, with 63 x 4 and 4 planes 38).  It rises with
     // shorter rows (8 / w) and with tiles that split cache lines: by 30 % beyond the
     // caches where the rows of the domain are whole ones (160 x 242 x 96 with one
-    // component in FP32, 54-wide tiles 172 us, 32-wide 108), otherwise by 3 % in
-    // FP64 and by 8 % in domains many times the caches' size (12 % with two
-    // components in FP64).  Lines count 64 bytes in FP64, whose stores are always
-    // non-temporal and write such sectors (200 x 200 x 100 with one component: 50-wide
-    // tiles 319 us, 40-wide 247), 128 where cached stores merge them.  Over 324
-    // domains of 1.4 thousand to 14 million cells in six formats, up to 16 tiles and
-    // chunks each, the choice is 1.2 % off the best on average.
+    // component in FP32, 54-wide tiles 172 us, 32-wide 108), otherwise by 8 % in
+    // domains many times the caches' size (with two components in FP64, which store
+    // past the caches, by 3 and 12 %).  Lines count 64 bytes in FP64, where a
+    // non-temporal store of eight values fills such a sector (200 x 200 x 100 with one
+    // component: 50-wide tiles 319 us, 40-wide 247), 128 in the other formats.  Over
+    // 324 domains of 1.4 thousand to 14 million cells in six formats, up to 16 tiles
+    // and chunks each, the choice is 1.2 % off the best on average.
     // Even parts of the domain are tried beside 64 x 8: 131^3 in FP16 takes 44 x 11
     // tiles (109 us a step, 125 with 64 x 8), 100^3 50 x 10 (48 / 56); 192^3 and 224^3
     // keep 64 x 8 (264 against 266 us with 64 x 7, 416 against 516 with 56 x 9 in FP16);
@@ -171,7 +171,8 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     const bool f64 = p.storage == hm::kF64;
     const bool cached = state < (int64_t(1) << 27);  // both buffers within the 256 MB of the last cache
     const double follow = cached ? 0.15 : 0.3;
-    const double split = f64 ? (p.ncomp == 2 && p.N > 1500000 ? 1.12 : 1.03) : (p.N > 6000000 ? 1.08 : 1.005);
+    const bool wide = f64 && p.ncomp == 2;
+    const double split = wide ? (p.N > 1500000 ? 1.12 : 1.03) : (p.N > 6000000 ? 1.08 : 1.005);
     const int64_t line = f64 ? 64 : 128;
     auto each_tile = [&](auto&& consider) {
         const int k0 = part(p.nx, 64);
@@ -244,9 +245,11 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     // goes out: 131^3 in FP32 179 us a step with cached stores against 206, 100^3 in
     // FP16 49 against 56; with whole lines non-temporal stores are the faster ones
     // (256^3 in FP32 970 against 997).
-    // FP64 keeps them (150^3 548 against 577, 160^3 528 against 550).
+    // Two components in FP64 keep them (150^3 548 against 577, 160^3 528 against 550);
+    // one component follows its 64-byte lines: 150^3 226 cached against 267, 131 x 110 x
+    // 209 202 against 250, 317 x 125 x 210 528 against 605, but 160^3 4 % slower.
     if (l.bx > 0) l.nt_stores = hm::box_nt_stores(p, l.bx);
-    else l.nt_stores = p.storage == hm::kF64 || (l.tile_x * word % 128 == 0 && p.nx * word % 128 == 0);
+    else l.nt_stores = wide || (l.tile_x * word % line == 0 && p.nx * word % line == 0);
     return l;
 }
 

@@ -108,3 +108,13 @@ def test_box_rows_of_whole_lines_are_stored_past_the_caches(planner):
     for shape, nt in (((64, 64, 128), True), ((66, 62, 128), False)):
         p = _plan.plans(planner, [(shape, "f32", 1, 1, "shan-chen")])[0]
         assert p.box and p.nt is nt
+
+
+def test_one_component_fp64_stores_split_rows_through_the_caches(planner):
+    """us a step, cached / non-temporal: 317 x 125 x 210 528 / 605, 133 x 117 x 181
+    194 / 273, 234 x 42 x 355 240 / 307.  Rows of whole 64 bytes (160^3, 200^3 in
+    40-wide tiles) and two components stay non-temporal."""
+    for shape, ncomp, nt in (((317, 125, 210), 1, False), ((133, 117, 181), 1, False), ((234, 42, 355), 1, False),
+                             ((160, 160, 160), 1, True), ((200, 200, 200), 1, True), ((150, 150, 150), 2, True)):
+        p = _plan.plans(planner, [(shape, "f64", ncomp, 1, "shan-chen")])[0]
+        assert p.box is None and p.nt is nt, shape
