@@ -123,11 +123,12 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     const int64_t word = hm::storage_bytes(p.storage) * (pair ? 2 : 1);
     auto part = [](int n, int k) { return (n + k - 1) / k; };
     // One block fits a CU (registers and LDS), so blocks run in rounds of one
-    // per CU, and a block takes about (chunk + 8) plane times: the halo planes,
+    // per CU, and a block takes about (chunk + fill) plane times: the halo planes,
     // the pipeline fill and drain and the block's start cost as much as about
-    // eight planes (fitted to timings of 192^3 to 384^3 domains).  Take the tile and
-    // chunking with the least rounds x (chunk + 8) x plane time, the fewest chunks
-    // among equals.  Two blocks fit a CU with one component in FP32 arithmetic and in
+    // eight planes (fitted to timings of 192^3 to 384^3 domains), as five in the
+    // 16-bit pair sweep, which keeps two planes of loads in flight: 254 x 268 x 30
+    // takes 64 x 7 tiles of 10 planes, 107 us a step, 129 with 64 x 5 of 30.  Take the tile and chunking with the least rounds x (chunk +
+    // fill) x plane time, the fewest chunks among equals.  Two blocks fit a CU with one component in FP32 arithmetic and in
     // thin domains, but share its time: over 123 domains with one component the
     // choices are 1.8 % off the best with one block counted per CU, 10 % with two.
     // Chunks shorter than 16 planes spend too much on their halo, unless the domain
@@ -140,7 +141,7 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     // on latency: 64 x 64 x 129 with 6 of 8 rows and 6 planes per block takes 45 us in
     // FP32 and 33 in FP16, whole 64 x 8 tiles of 5 planes 41 and 29; 63^3 in FP64
     // with 63 x 2 and 8 planes 54, with 63 x 4 and 4 planes 38).  It rises with
-    // shorter rows (8 / w) and with tiles that split cache lines: by 30 % beyond the
+    // shorter rows (8 / w, 10 / w in the 16-bit pair sweep) and with tiles that split cache lines: by 30 % beyond the
     // caches where the rows of the domain are whole ones (160 x 242 x 96 with one
     // component in FP32, 54-wide tiles 172 us, 32-wide 108), otherwise by 8 % in
     // domains many times the caches' size (with two components in FP64, which store
@@ -171,6 +172,9 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     const bool f64 = p.storage == hm::kF64;
     const bool cached = state < (int64_t(1) << 27);  // both buffers within the 256 MB of the last cache
     const double follow = cached ? 0.15 : 0.3;
+    const bool half = pair && p.storage != hm::kF32;
+    const int fill = half ? 5 : 8;
+    const double narrow_row = half ? 10.0 : 8.0;
     const bool wide = f64 && p.ncomp == 2;
     const double split = wide ? (p.N > 1500000 ? 1.12 : 1.03) : (p.N > 6000000 ? 1.08 : 1.005);
     const int64_t line = f64 ? 64 : 128;
@@ -219,13 +223,13 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
         const double lanes = lanes_of(cols, l.cells);
         const double lines = (h * w == l.cells && w % 32 == 0 ? 1.0 : split) *
                              (!cached && p.nx * word % line == 0 && w * word % line != 0 ? 1.3 : 1.0);
-        const double plane = (1.0 - follow + follow * lanes) * (1.0 + 8.0 / w) * lines;
+        const double plane = (1.0 - follow + follow * lanes) * (1.0 + narrow_row / w) * lines;
         const int64_t tiles16 = cols * ((p.nz + 15) / 16);
         const int min_chunk = tiles16 >= 2 * ncu ? 16 : 4;
         // the distinct chunk lengths of even parts of nz, longest first
         for (int z = env_z ? std::min(std::max(env_z, 1), p.nz) : p.nz;;) {
             const int64_t blocks = cols * part(p.nz, z);
-            const double cost = static_cast<double>(((blocks + ncu - 1) / ncu) * (z + 8)) * plane;
+            const double cost = static_cast<double>(((blocks + ncu - 1) / ncu) * (z + fill)) * plane;
             if (best < 0.0 || cost < best) {
                 best = cost;
                 l.tile_x = w;

@@ -25,6 +25,10 @@ TIMES = {
     ((160, 242, 96), "f32", 1): {(64, 6, 48): 119.1, (32, 15, 32): 107.7, (54, 9, 32): 172.3},
     ((200, 200, 100), "f64", 1): {(64, 8, 20): 260.0, (40, 12, 34): 247.0, (50, 10, 34): 321.0},
     ((200, 200, 200), "f64", 1): {(64, 8, 40): 499.7, (40, 12, 67): 471.9, (50, 10, 67): 652.4},
+    # flat: a chunk's halo and pipeline fill cost less than idle lanes' planes
+    ((254, 268, 30), "f16s", 2): {(64, 8, 10): 106.3, (64, 7, 10): 107.6, (64, 5, 30): 128.0, (64, 8, 30): 128.7},
+    ((160, 160, 160), "f16s", 2): {(32, 16, 32): 167.3, (64, 8, 40): 176.9},
+    ((224, 224, 224), "f16s", 2): {(64, 8, 112): 418.9, (64, 8, 25): 440.3, (32, 16, 45): 442.3},
     # rows that split lines anyway keep the fitted tiles
     ((131, 131, 131), "f16s", 2): {(44, 11, 19): 108.2, (64, 8, 27): 124.8},
     ((131, 131, 131), "f64", 2): {(44, 5, 44): 363.9, (64, 4, 27): 407.1},
