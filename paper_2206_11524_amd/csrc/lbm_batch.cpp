@@ -4,9 +4,9 @@
 // Both drive the batched step kernel through a BatchRunner: two device copies
 // of the domain table (double-buffered so the host can encode tick k+1 while
 // tick k still reads its table), pinned staging, and captured HIP graphs of K
-// launches (one per table copy and store policy).  A launch k advances every domain whose
-// step count for the tick exceeds k, so domains with different remaining
-// budgets share one graph.
+// launches (one per table copy and store policy).  A launch k advances every
+// domain whose step count for the tick exceeds k, so domains with different
+// remaining budgets share one graph.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

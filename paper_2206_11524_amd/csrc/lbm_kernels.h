@@ -40,7 +40,7 @@ struct Launch {
     int tile_y;   // rows per tile, within tile_limits
     int zchunk;   // planes per block
     int cells;    // cells of a block of the sweep (block_cells)
-    bool nt_stores;  // non-temporal stores (always in the sweep in FP64)
+    bool nt_stores;  // non-temporal stores (always in the sweep of two components in FP64)
     int bx, by, bz;  // cells per block of the box kernel (small domains); bx = 0: the sweep
     int batch_x, batch_y;  // tile in a batched launch
 };

@@ -418,7 +418,7 @@ __device__ __forceinline__ void step_tile(const Args<typename ST::T>& a, const t
 // components of a cell meet in registers, so the first moments need no LDS
 // exchange; the densities still go to LDS for the force stencils.
 //
-// The waves of a block have fixed roles.  The first kPairCells threads own one
+// The waves of a block have fixed roles.  The first CELLS threads own one
 // cell each: they pull, collide and store it, with the next plane's loads in
 // flight.  The last NR threads (whole waves) stage the one-cell ring of
 // densities around the tile and the n_s planes: they hold no collision state,
@@ -752,8 +752,9 @@ __global__ __launch_bounds__((kThreads<ST, NC, FS, CELLS>)) void k_step(Args<typ
 {
     // One block fits a CU, two with one component in FP32 arithmetic (77 KB of
     // LDS) and, but for two n_s fields with the GS-WBS, with the smaller blocks of
-    // thin domains: a round of the 256 CUs is 256 or 512 blocks.  Runs per round instead of one run of the whole grid: 181^3 in FP64,
-    // 690 blocks, 948 us against 1050.
+    // thin domains: a round of the 256 CUs is 256 or 512 blocks.  Runs per round
+    // instead of one run of the whole grid: 181^3 in FP64, 690 blocks, 948 us against
+    // 1050.
     constexpr bool TWO = CELLS < kBlockCells<ST, NC, FS> || (NC == 1 && sizeof(typename ST::T) == 4);
     const int L = xcd_tile(blockIdx.x, gridDim.x, TWO ? 512 : 256);
     if constexpr (kPair<ST, NC, FS>) {
@@ -1338,8 +1339,8 @@ static hipError_t step_t(const Problem& p, const Launch& l, int64_t t, const voi
     a.t = static_cast<uint32_t>(t);
     const int nblocks = a.ntx * a.nty * a.nzc;
     // one instance per block size and store policy (two components in FP64 and one
-    // plane keep non-temporal stores), and of the pair kernel per rounding mode; the split
-    // kernels branch on it (their two store sequences are alike)
+    // plane keep non-temporal stores), and of the pair kernel per rounding mode;
+    // the split kernels branch on it (their two store sequences are alike)
     constexpr int CELLS = kBlockCells<ST, NC, FS>;
     auto go = [&](auto rnd, auto aux, auto cells) {
         constexpr int NB = decltype(cells)::value;

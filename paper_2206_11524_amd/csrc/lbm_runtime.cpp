@@ -127,10 +127,12 @@ hm::Launch choose_launch(const hm::Problem& p, int cus, bool batched)
     // the pipeline fill and drain and the block's start cost as much as about
     // eight planes (fitted to timings of 192^3 to 384^3 domains), as five in the
     // 16-bit pair sweep, which keeps two planes of loads in flight: 254 x 268 x 30
-    // takes 64 x 7 tiles of 10 planes, 107 us a step, 129 with 64 x 5 of 30.  Take the tile and chunking with the least rounds x (chunk +
-    // fill) x plane time, the fewest chunks among equals.  Two blocks fit a CU with one component in FP32 arithmetic and in
-    // thin domains, but share its time: over 123 domains with one component the
-    // choices are 1.8 % off the best with one block counted per CU, 10 % with two.
+    // takes 64 x 7 tiles of 10 planes, 107 us a step, 129 with 64 x 5 of 30.  Take
+    // the tile and chunking with the least rounds x (chunk + fill) x plane time,
+    // the fewest chunks among equals.  Two blocks fit a CU with one component in
+    // FP32 arithmetic and in thin domains, but share its time: over 123 domains
+    // with one component the choices are 1.8 % off the best with one block counted
+    // per CU, 10 % with two.
     // Chunks shorter than 16 planes spend too much on their halo, unless the domain
     // would then give fewer than two such tiles per CU: a small domain would leave
     // most CUs idle, and its halo re-reads are L2 hits.
